@@ -280,11 +280,12 @@ constexpr int KS_ROW_BYTES = 256;   // contiguous bytes wanted per row of a tile
 constexpr long KS_LDS = 163840;     // LDS budget of a tile
 constexpr int KS_NT = 1024;         // threads of a workgroup when the tile has that many modes
 // kx values per workgroup: KXT * NS * sizeof(complex) >= KS_ROW_BYTES contiguous bytes where the
-// LDS tile allows
+// LDS tile allows, and at most 16: the rows are padded to a multiple of 16 kx, so that a tile of more
+// would reach into (and store over) the next row, another workgroup's
 template <typename T, int N, int NS> constexpr int kspace_kxt() {
   constexpr int want = (KS_ROW_BYTES + NS * (int)sizeof(cplx<T>) - 1) / (NS * (int)sizeof(cplx<T>));
   int k = 1;
-  while (k < want) k *= 2;
+  while (k < want && k < 16) k *= 2;
   while (k > 1 && (long)N * k * NS * (long)sizeof(cplx<T>) > KS_LDS) k /= 2;
   return k;
 }

@@ -144,6 +144,24 @@ def test_zeldovich_32_fp64_scalar_ten_steps():
     assert steps == 10 and abs(a - 0.05) < 1e-12
 
 
+@pytest.mark.parametrize("n", [16, 64])
+def test_newtonian_fp32_steps(n):
+    """One source component: the Fourier-space tiles end inside the padded rows (n = 16: 16 kx, 64: 48)."""
+    _say(f"newtonian fp32 n={n}")
+    pos, u, tau0, dtau = config_particles("zeldovich_32_scalar_fp64", n=n)
+    u = u.astype(np.float32)
+    ctx = _ctx(n, pos.shape[0], 320.0, "newtonian", "fp32")
+    ctx.init_particles(pos, u, tau0)
+    sim = opm.OracleSim(n=n, box_mpch=320.0, physics="newtonian", pos=pos, u=u, tau=tau0)
+    for _ in range(3):
+        ctx.step(dtau)
+        sim.step(dtau)
+    phi = ctx.get_field("phi").astype(np.float64)
+    assert rel_l2(phi, sim.phi) < FIELD_TOL["fp32"]
+    gp, _ = ctx.get_particles()
+    assert periodic_max_dx(gp, sim.particles_by_id()[0], n) < POS_TOL["fp32"]
+
+
 @pytest.mark.parametrize("physics", ["newtonian", "full"])
 def test_fp64_step_parity_physics(physics):
     _say(f"fp64 {physics}")

@@ -30,7 +30,7 @@ struct Layout {
   size_t pos2[2], mom2[2], ids2[2], rank2, cnt2, cell_start2;
   size_t dep, part, phi[3], chi, b[3], spec, spec_out, hst, a2b, tw, kt, rowsum, scal, err;
   // learned closure (PM_FLAG_CLOSURE): activations, gradients, packed weights, partials
-  size_t cl_act[3], cl_dact[3], cl_corr, cl_dcorr, cl_wf, cl_wb, cl_bias, cl_part, cl_scal;
+  size_t cl_act[3], cl_dact[3], cl_corr, cl_wf, cl_wb, cl_bias, cl_part, cl_scal;
   bool closure, cl_train;
   size_t total;
   int ndep, nsrc, nout, nhp;
@@ -103,7 +103,6 @@ Layout make_layout(const pm_config& c) {
     L.cl_train = n <= 256;
     if (L.cl_train) {
       for (int i = 0; i < 3; ++i) L.cl_dact[i] = take(n3 * 32);
-      L.cl_dcorr = take(3 * n3 * 4);
       L.cl_part = take((size_t)closure_wgrad_part_bytes(n));
     }
   }
@@ -1288,12 +1287,6 @@ pm_status pm_closure_backward(pm_ctx* c, const float* d_dpred, float* d_grad) {
   if (!L.cl_train) return c->fail(PM_EUNSUPPORTED, "closure training needs n_mesh <= 256");
   if (!c->cl_forwarded) return c->fail(PM_ESTATE, "closure_backward needs closure_forward");
   const int n = c->n;
-  float* dcorr = c->at<float>(L.cl_dcorr);
-  c->zero(L.cl_dcorr, 3 * c->n3 * 4);
-  if (c->cfg.precision == PM_FP64)
-    closure_gather3_adjoint<double>(c->parts<double>(c->cur), c->np, n, d_dpred, dcorr, c->st);
-  else
-    closure_gather3_adjoint<float>(c->parts<float>(c->cur), c->np, n, d_dpred, dcorr, c->st);
   uint16_t* d3 = c->at<uint16_t>(L.cl_dact[2]);
   uint16_t* d2 = c->at<uint16_t>(L.cl_dact[1]);
   uint16_t* d1 = c->at<uint16_t>(L.cl_dact[0]);
@@ -1302,7 +1295,11 @@ pm_status pm_closure_backward(pm_ctx* c, const float* d_dpred, float* d_grad) {
   const uint16_t* a2 = c->at<uint16_t>(L.cl_act[2]);
   const uint16_t* wb = c->at<uint16_t>(L.cl_wb);
   float* part = c->at<float>(L.cl_part);
-  closure_soa3_to_bf16(dcorr, c->n3, d3, c->st);
+  auto adjoint = [&](const auto& p) {
+    launch_deposit_vectors(p.px, p.py, p.pz, p.id, c->at<uint32_t>(L.cell_start), n, d_dpred, d3, c->st);
+  };
+  if (c->cfg.precision == PM_FP64) adjoint(c->parts<double>(c->cur));
+  else adjoint(c->parts<float>(c->cur));
   const long off2 = 16 * 4 * 27 + 16, off3 = off2 + 16 * 16 * 27 + 16;
   closure_wgrad(a2, d3, n, part, 16, 3, d_grad, off3, c->st);
   closure_conv(d3, wb + 2 * 27 * 256, nullptr, n, 2, d2, a2, nullptr, c->st);

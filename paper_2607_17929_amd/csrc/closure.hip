@@ -25,15 +25,6 @@ namespace gpm {
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// round-to-nearest-even float -> bfloat16 bits
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // NaN stays NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-
 constexpr int CV_TX = 16, CV_TY = 8, CV_TZ = 4, CV_NT = 256;
 constexpr int CV_HX = CV_TX + 2, CV_HY = CV_TY + 2, CV_HZ = CV_TZ + 2;
 constexpr int CV_HP = CV_HX * CV_HY * CV_HZ;  // halo points
@@ -479,40 +470,6 @@ __global__ __launch_bounds__(256) void cube_symmetry_kernel(long np, int p0, int
   }
 }
 
-// adjoint of gather3: FP32 atomics into a zeroed SoA field (training sizes only)
-template <typename T>
-__global__ __launch_bounds__(256) void gather3_adjoint_kernel(Particles<T> p, long np, int n,
-                                                              const float* __restrict__ vals, float* __restrict__ f) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= np) return;
-  int x0, x1, y0, y1, z0, z1;
-  float wx0, wx1, wy0, wy1, wz0, wz1;
-  cic(p.px[i], n, x0, x1, wx0, wx1);
-  cic(p.py[i], n, y0, y1, wy0, wy1);
-  cic(p.pz[i], n, z0, z1, wz0, wz1);
-  const long nn = (long)n * n, n3 = nn * n;
-  const long id = p.id[i];
-  const int zs[2] = {z0, z1}, ys[2] = {y0, y1}, xs[2] = {x0, x1};
-  const float wz[2] = {wz0, wz1}, wy[2] = {wy0, wy1}, wx[2] = {wx0, wx1};
-  for (int c = 0; c < 3; ++c) {
-    const float v = vals[3 * id + c];
-    for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b)
-        for (int d = 0; d < 2; ++d)
-          atomicAdd(&f[c * n3 + zs[a] * nn + ys[b] * n + xs[d]], v * wz[a] * wy[b] * wx[d]);
-  }
-}
-
-// FP32 SoA [3][n^3] -> bfloat16 [p][16] (channels 3..15 zero)
-__global__ __launch_bounds__(256) void soa3_to_bf16_kernel(const float* __restrict__ f, long n3, uint16_t* out) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n3) return;
-  uint4 a = make_uint4((uint32_t)f2bf(f[i]) | ((uint32_t)f2bf(f[n3 + i]) << 16), (uint32_t)f2bf(f[2 * n3 + i]), 0u, 0u);
-  uint4* o = reinterpret_cast<uint4*>(out + i * 16);
-  o[0] = a;
-  o[1] = make_uint4(0u, 0u, 0u, 0u);
-}
-
 // gradient of phi (centred differences, CIC-interpolated) at the particles, identifier order
 template <typename T>
 __global__ __launch_bounds__(256) void gather_grad_phi_kernel(Particles<T> p, long np, int n, const T* __restrict__ phi,
@@ -622,16 +579,6 @@ void closure_cube_symmetry(long np, const int perm[3], int flip, const double* p
 }
 
 template <typename T>
-void closure_gather3_adjoint(const Particles<T>& p, long np, int n, const float* vals, float* f, hipStream_t st) {
-  hipLaunchKernelGGL((gather3_adjoint_kernel<T>), dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, p, np, n, vals,
-                     f);
-}
-
-void closure_soa3_to_bf16(const float* f, long n3, uint16_t* out, hipStream_t st) {
-  hipLaunchKernelGGL(soa3_to_bf16_kernel, dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0, st, f, n3, out);
-}
-
-template <typename T>
 void gather_grad_phi(const Particles<T>& p, long np, int n, const T* phi, T* out, hipStream_t st) {
   hipLaunchKernelGGL((gather_grad_phi_kernel<T>), dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, p, np, n, phi,
                      out);
@@ -640,7 +587,6 @@ void gather_grad_phi(const Particles<T>& p, long np, int n, const T* phi, T* out
 #define GPM_CL_INST(T)                                                                                          \
   template void closure_features<T>(const T*, const T*, int, const double*, double*, float*, uint16_t*, hipStream_t); \
   template void closure_gather3<T>(const Particles<T>&, long, int, const float*, float*, hipStream_t);          \
-  template void closure_gather3_adjoint<T>(const Particles<T>&, long, int, const float*, float*, hipStream_t);  \
   template void closure_loss3<T>(const Particles<T>&, long, int, const float*, const float*, float*, double*,     \
                                  double*, hipStream_t);                                                          \
   template void gather_grad_phi<T>(const Particles<T>&, long, int, const T*, T*, hipStream_t);

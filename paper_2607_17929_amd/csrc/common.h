@@ -100,6 +100,15 @@ template <> __device__ __forceinline__ float rcp<float>(float x) { return __buil
 template <typename T> __device__ __forceinline__ T rsqrt_(T x) { return (T)1 / sqrt(x); }
 template <> __device__ __forceinline__ float rsqrt_<float>(float x) { return __builtin_amdgcn_rsqf(x); }
 
+// round-to-nearest-even float -> bfloat16 bits
+__device__ __forceinline__ uint16_t f2bf(float f) {
+  uint32_t u = __float_as_uint(f);
+  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // NaN stays NaN
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return (uint16_t)(u >> 16);
+}
+__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
+
 // Workgroups of a launch go to the 8 XCDs in turn (workgroup b to XCD b mod 8),
 // and each XCD has its own L2.  xcd_remap turns the hardware index into a
 // logical one under which every XCD walks one contiguous range, so that

@@ -124,6 +124,10 @@ int deposit_blocks(int n);
 template <typename T>
 void launch_deposit(const Particles<T>& p, const uint32_t* cell_start, int n, int ncomp, bool relativistic, double a,
                     double weight, bool accumulate, T* dep, double* esum_part, hipStream_t st);
+// sum over particles of W vals[id] ([np][3] in identifier order) as bfloat16 [vertex][16], channels 3 .. 15 zero:
+// the adjoint of the closure's gather
+void launch_deposit_vectors(const double* px, const double* py, const double* pz, const uint32_t* id,
+                            const uint32_t* cell_start, int n, const float* vals, uint16_t* out, hipStream_t st);
 template <typename T>
 struct GatherArgs {
   const T* phi; const T* chi; const T* bx; const T* by; const T* bz;
@@ -166,8 +170,6 @@ void closure_features(const T* n00, const T* phi, int n, const double* n00_sum, 
                       uint16_t* out, hipStream_t st);
 template <typename T>
 void closure_gather3(const Particles<T>& p, long np, int n, const float* f, float* out, hipStream_t st);
-template <typename T>
-void closure_gather3_adjoint(const Particles<T>& p, long np, int n, const float* vals, float* f, hipStream_t st);
 // pred - target at the particles: dpred = 2 (pred - target) / (3 np), out[0] = mean |pred - target|^2,
 // out[1] = mean |target|^2 (FP64); part holds 2 x 512 doubles of scratch
 template <typename T>
@@ -175,7 +177,6 @@ void closure_loss3(const Particles<T>& p, long np, int n, const float* f, const 
                    double* part, double* out, hipStream_t st);
 void closure_cube_symmetry(long np, const int perm[3], int flip, const double* pos, const float* u, const float* v,
                            double* pos_out, float* u_out, float* v_out, hipStream_t st);
-void closure_soa3_to_bf16(const float* f, long n3, uint16_t* out, hipStream_t st);
 template <typename T>
 void gather_grad_phi(const Particles<T>& p, long np, int n, const T* phi, T* out, hipStream_t st);
 

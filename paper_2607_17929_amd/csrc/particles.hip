@@ -84,9 +84,20 @@ void launch_ingest(const double* pos_aos, const T* u_aos, const uint32_t* ids, l
 // offsets of the staged lists are scanned in LDS, three planes in flight).
 // Only cell_start and the particle arrays are read; each vertex is written once.
 // ---------------------------------------------------------------------------
-constexpr int DEP_NT = 256;                  // one vertex column per thread
-template <typename T> constexpr int dep_cap() { return sizeof(T) == 4 ? 512 : 256; }  // staged particles per chunk
-constexpr int DEP_ZB = 16;                   // vertex planes per workgroup (fewer on small meshes)
+// Workgroups of 256 threads and 32 x 8 vertex columns, on the largest meshes 128 threads and 32 x 4 (512^3 clustered
+// 4.33 ms against 4.76; at 128^3 and 256^3 they are 0.26 against 0.22 and 0.43 against 0.42 ms): one column a thread.
+__host__ __device__ constexpr int dep_nt(int n) { return n >= 512 ? 128 : 256; }
+// staged particles per chunk: a plane of mean density fits one (33 x 9 or 33 x 5 cells), in FP64 with three waves a SIMD
+template <typename T, int NT> constexpr int dep_cap() { return sizeof(T) == 4 ? 2 * NT : 3 * NT / 2; }
+// Vertex planes per workgroup: 16, and fewer where that leaves fewer than DEP_WAVES waves (four rounds of 16 on
+// every CU): a 32^3 mesh in 16-plane columns is 8 workgroups that walk 17 cell planes each (78 us; 17 us with
+// single planes), a clustered 128^3 mesh 512 of them (0.38 ms; 0.25 with 8 planes, 0.22 with 4).
+constexpr int DEP_ZB = 16, DEP_WAVES = 16384;
+// A cell of this many particles or more is summed by the whole wave on the matrix cores (crowded_cell below): in the
+// lane loop its n particles cost a lane of each of 4 vertex columns 45 n instructions while 60 others wait, here
+// n / 4 matrix products and about 100 instructions.  12 and 16 measure alike, 8 is 2 % slower (512^3 clustered,
+// cells of up to 690: deposit 5.77 -> 4.4 ms; 256^3 1.11 -> 0.80; FP64 256^3 1.47 -> 1.07 ms).
+constexpr uint32_t DEP_CROWD = 12;
 
 __host__ __device__ constexpr int dep_tx(int n) { return n >= 32 ? 32 : 16; }
 
@@ -113,6 +124,8 @@ __device__ __forceinline__ int row_of(const uint32_t* off, uint32_t i) {
   return lo;
 }
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+
 // One particle in registers (loaded for the next plane while the current one is summed).
 template <typename T>
 struct DepPart {
@@ -120,23 +133,27 @@ struct DepPart {
   T ux, uy, uz;
 };
 
-template <typename T, int NC, bool REL, int TX>
-__global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const uint32_t* __restrict__ cell_start, int n,
+template <typename T, int NC, bool REL, int TX, int DEP_NT>
+__global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel(Particles<T> p, const uint32_t* __restrict__ cell_start, int n,
                                                          int zb, T a, double a64, T w, double wd, int accumulate,
-                                                         T* __restrict__ dep, double* __restrict__ esum) {
+                                                         T* __restrict__ dep, double* __restrict__ esum,
+                                                         const float* __restrict__ vals) {
   constexpr int TY = DEP_NT / TX, ROWS = TY + 1, RW = TX + 3;  // raw offsets per row: halo start/end, x0 .. x0 + TX
-  constexpr int CAP = dep_cap<T>(), SPT = CAP / DEP_NT;
+  constexpr int CAP = dep_cap<T, DEP_NT>(), SPT = (CAP + DEP_NT - 1) / DEP_NT;
   constexpr int NQ = (ROWS * RW + DEP_NT - 1) / DEP_NT;
   constexpr int N4 = NC < 4 ? NC : 4, N6 = NC > 4 ? NC - 4 : 1;
   constexpr int WX = TX >= 16 ? 16 : TX, WY = 64 / WX;         // a wave's vertex columns: WX x WY
-  static_assert(ROWS <= 64 && CAP % DEP_NT == 0 && TX % WX == 0 && TY % WY == 0, "tile shape");
-  constexpr int C4 = NC > 1 ? CAP : 1;
+  static_assert(ROWS <= 64 && TX % WX == 0 && TY % WY == 0, "tile shape");
+  constexpr bool CROWD = NC > 1;              // (a count takes so little that the test for crowded cells costs more)
+  constexpr bool VEC = NC == 3;               // sums of W v for the 3-vectors vals[id] instead of the stress-energy
+  constexpr int C4 = NC > 1 ? CAP : 1, C6 = NC > 4 ? CAP : 1;
   __shared__ V4<T> sfr[CAP];                  // f_x, f_y, f_z, -
-  __shared__ V4<T> sq[C4], ss[C4];            // (e, u_x, u_y, u_z), (u_x u_x, u_x u_y, u_x u_z, u_y u_y) / e
-  __shared__ T ss2[C4][2];                    // (u_y u_z, u_z u_z) / e
+  __shared__ V4<T> sq[C4], ss[C6];            // (e, u_x, u_y, u_z), (u_x u_x, u_x u_y, u_x u_z, u_y u_y) / e
+  __shared__ T ss2[C6][2];                    // (u_y u_z, u_z u_z) / e
   __shared__ uint32_t raw[3][ROWS][RW];       // cell offsets of the planes in flight (plane mod 3)
   __shared__ uint32_t roff[3][ROWS + 1];      // staged offset of each row
   __shared__ double red[DEP_NT / 64];
+  __shared__ double scr[CROWD ? DEP_NT / 64 : 1][8][NC];  // corner sums of a crowded cell
   const int m = n - 1;
   int bx, by, bz;
   xcd_block3(bx, by, bz);
@@ -146,12 +163,21 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
   const int lvx = (wave % (TX / WX)) * WX + lane % WX, lvy = (wave / (TX / WX)) * WY + lane / WX;
   const long nn = (long)n * n, n3 = nn * n;
 
+  // the thread index as a value of this place: with ten quantities, what is formed from it is formed again in
+  // every plane instead of being kept in registers through all of them (the sums and the prefetch fill the
+  // 128 registers of four waves a SIMD; a few spilled ones cost 8 to 20 % of the kernel's time)
+  auto here = [&]() {
+    int t = tid;
+    if constexpr (NC > 4) asm volatile("" : "+v"(t));
+    return t;
+  };
   // raw cell offsets of cell plane cz: row r is cell row y0 - 1 + r; entry 0/1 = start/end of the
   // halo cell x0 - 1, entry 2 + j = start of cell x0 + j (j = 0 .. TX)
   auto load_raw = [&](int cz, uint32_t* v) {
+    const int t0 = here();
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-      const int q = tid + k * DEP_NT;
+      const int q = t0 + k * DEP_NT;
       if (q < ROWS * RW) {
         const int r = q / RW, j = q - r * RW;
         const uint32_t rb = ((uint32_t)(cz & m) * (uint32_t)n + (uint32_t)((y0 - 1 + r) & m)) * (uint32_t)n;
@@ -161,9 +187,10 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
     }
   };
   auto store_raw = [&](int b, const uint32_t* v) {
+    const int t0 = here();
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-      const int q = tid + k * DEP_NT;
+      const int q = t0 + k * DEP_NT;
       if (q < ROWS * RW) raw[b][q / RW][q % RW] = v[k];
     }
   };
@@ -185,7 +212,12 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
   };
   auto load_part = [&](uint32_t g, DepPart<T>& d) {
     d.x = p.px[g]; d.y = p.py[g]; d.z = p.pz[g];
-    if constexpr (NC > 1) { d.ux = p.ux[g]; d.uy = p.uy[g]; d.uz = p.uz[g]; }
+    if constexpr (VEC) {
+      const long id = p.id[g];
+      d.ux = vals[3 * id]; d.uy = vals[3 * id + 1]; d.uz = vals[3 * id + 2];
+    } else if constexpr (NC > 1) {
+      d.ux = p.ux[g]; d.uy = p.uy[g]; d.uz = p.uz[g];
+    }
   };
   double e_own = 0.0;
   auto stage = [&](uint32_t l, const DepPart<T>& d, bool own) {
@@ -196,7 +228,9 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
     fr.z = (T)(sz - floor(sz));
     fr.w = (T)0;
     sfr[l] = fr;
-    if constexpr (NC > 1) {
+    if constexpr (VEC) {
+      sq[l] = V4<T>{d.ux, d.uy, d.uz, (T)0};
+    } else if constexpr (NC > 1) {
       const T vx = d.ux, vy = d.uy, vz = d.uz;
       const T u2 = vx * vx + vy * vy + vz * vz;
       const T e = REL ? sqrt(a * a + u2) : a;
@@ -229,11 +263,54 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
 #pragma unroll
   for (int c = 0; c < N6; ++c) lo6[c] = hi6[c] = (T)0;
 
+  // The 8 corner sums of one crowded cell's n staged particles from b0 on, by the whole wave on the
+  // matrix cores: a 16x16x4 FP64 product of corner weights (rows) and quantities (columns) over the
+  // particles, four to an instruction; lane l feeds row and column l % 16 of particle l / 16.  The sums
+  // go through the wave's scratch to the lanes of the cell's 4 vertex columns (cell c, row r of the tile).
+  auto crowded_cell = [&](uint32_t b0, uint32_t n, int c, int r) {
+    const int mcol = here() & 15, mk4 = (here() & 63) >> 4;
+    const T* qbase = nullptr;  // quantity mcol of staged particle 0 and its stride
+    int qstride = 4;
+    if constexpr (NC > 1) {
+      qbase = reinterpret_cast<const T*>(NC < 4 || mcol < 4 ? sq : ss) + (mcol & 3);
+      if (NC > 8 && mcol >= 8) { qbase = &ss2[0][mcol & 1]; qstride = 2; }
+    }
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+    for (uint32_t k0 = 0; k0 < n; k0 += 4) {
+      const uint32_t k = k0 + mk4;
+      const uint32_t l = b0 + min(k, n - 1);  // beyond the last particle: its values with weight zero
+      const V4<T> fr = sfr[l];
+      const T wx = (mcol & 1) ? fr.x : (T)1 - fr.x;
+      const T wxy = wx * ((mcol & 2) ? fr.y : (T)1 - fr.y);
+      const T wh = wxy * fr.z;
+      const T w8 = (k < n && mcol < 8) ? ((mcol & 4) ? wh : wxy - wh) : (T)0;
+      T q = a;
+      if constexpr (NC > 1) q = qbase[l * qstride];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)w8, (double)q, acc, 0, 0, 0);
+    }
+    // rows l / 16 (lower face) and 4 + l / 16 (upper face) of column l % 16
+    if (mcol < NC) {
+      scr[wave][mk4][mcol] = acc[0];
+      scr[wave][4 + mk4][mcol] = acc[1];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const uint32_t ox = (uint32_t)(c - lvx), oy = (uint32_t)(r - lvy);
+    if (ox <= 1u && oy <= 1u) {
+      const int xy = (int)((1u - ox) + 2u * (1u - oy));
+#pragma unroll
+      for (int q = 0; q < N4; ++q) { lo4[q] += scr[wave][xy][q]; hi4[q] += scr[wave][4 + xy][q]; }
+#pragma unroll
+      for (int q = 4; q < NC; ++q) { lo6[q - 4] += (T)scr[wave][xy][q]; hi6[q - 4] += (T)scr[wave][4 + xy][q]; }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+
   // sum the staged particles [c0, c1) of the plane in buffer b: the thread's cells are, in the cell
   // rows lvy (below the vertex: weight f_y) and lvy + 1 (1 - f_y), the local cells lvx (x0 + lvx - 1,
-  // weight f_x) and lvx + 1 (1 - f_x), one contiguous staged range per row
+  // weight f_x) and lvx + 1 (1 - f_x), one contiguous staged range per row.  Cells of DEP_CROWD
+  // particles or more are left to the wave (crowded_cell): one of them would hold up 63 other lanes.
   auto accumulate_chunk = [&](int b, uint32_t c0, uint32_t c1) {
-    uint32_t beg[2], spl[2], len[2];
+    uint32_t beg[2], spl[2], end[2];
 #pragma unroll
     for (int dy = 0; dy < 2; ++dy) {
       const int r = lvy + dy;
@@ -242,11 +319,38 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
       const uint32_t s0 = ro + (lvx == 0 ? 0u : hn + (rr[1 + lvx] - m0));
       const uint32_t s1 = ro + hn + (rr[2 + lvx] - m0);
       const uint32_t s2 = ro + hn + (rr[3 + lvx] - m0);
-      const uint32_t bb = max(s0, c0), ee = min(s2, c1);
+      const uint32_t bb = max(s0, c0), ee = max(min(s2, c1), bb);
       beg[dy] = bb - c0;
-      spl[dy] = s1 > c0 ? s1 - c0 : 0u;
-      len[dy] = ee > bb ? ee - bb : 0u;
+      end[dy] = ee - c0;
+      spl[dy] = (CROWD ? min(max(s1, bb), ee) : max(s1, c0)) - c0;
     }
+    if constexpr (CROWD) {
+      const uint32_t most = max(max(spl[0] - beg[0], end[0] - spl[0]), max(spl[1] - beg[1], end[1] - spl[1]));
+      if (__ballot(most >= DEP_CROWD)) {
+        // the wave's crowded cells: each lane answers for the cell below and left of its vertex, the
+        // lanes at the patch's upper edges for the cells beyond them too
+        const bool ex = lane % WX == WX - 1, ey = lane / WX == WY - 1;
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+          const bool right = q & 1, up = q >> 1;
+          const uint32_t lb = up ? +beg[1] : +beg[0], lm = up ? +spl[1] : +spl[0], le = up ? +end[1] : +end[0];
+          const uint32_t cb = right ? +lm : +lb, cn = (right ? +le : +lm) - cb;
+          uint64_t m = __ballot((!right || ex) && (!up || ey) && cn >= DEP_CROWD);
+          while (m) {
+            const int src = __builtin_ctzll(m);
+            m &= m - 1;
+            crowded_cell(__builtin_amdgcn_readlane(cb, src), __builtin_amdgcn_readlane(cn, src),
+                         (wave % (TX / WX)) * WX + src % WX + (q & 1), (wave / (TX / WX)) * WY + src / WX + (q >> 1));
+          }
+        }
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+          if (spl[dy] - beg[dy] >= DEP_CROWD) beg[dy] = spl[dy];
+          if (end[dy] - spl[dy] >= DEP_CROWD) end[dy] = spl[dy];
+        }
+      }
+    }
+    const uint32_t len[2] = {end[0] - beg[0], end[1] - beg[1]};
     const uint32_t tot = len[0] + len[1];
     for (uint32_t j = 0; j < tot; ++j) {
       const bool r1 = j >= len[0];
@@ -259,6 +363,11 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
       if constexpr (NC == 1) {
         lo4[0] += (double)(wl * a);
         hi4[0] += (double)(wh * a);
+      } else if constexpr (VEC) {
+        const V4<T> q = sq[l];
+        const double dl = (double)wl, dh = (double)wh;
+        lo4[0] = fma(dl, (double)q.x, lo4[0]); lo4[1] = fma(dl, (double)q.y, lo4[1]); lo4[2] = fma(dl, (double)q.z, lo4[2]);
+        hi4[0] = fma(dh, (double)q.x, hi4[0]); hi4[1] = fma(dh, (double)q.y, hi4[1]); hi4[2] = fma(dh, (double)q.z, hi4[2]);
       } else {
         const V4<T> q = sq[l], t = ss[l];
         const T t4 = ss2[l][0], t5 = ss2[l][1];
@@ -313,20 +422,20 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
     const uint32_t total = roff[b][ROWS];
     // 1. the prefetched first chunk of this plane into LDS
     {
-      const uint32_t lim = min(total, (uint32_t)CAP);
+      const uint32_t lim = min(total, (uint32_t)CAP), t0 = here();
 #pragma unroll
       for (int s2 = 0; s2 < SPT; ++s2) {
-        const uint32_t i = tid + s2 * DEP_NT;
+        const uint32_t i = t0 + s2 * DEP_NT;
         if (i < lim) stage(i, pr[s2], pown[s2]);
       }
     }
     __syncthreads();
     // 2. requests for the next planes: particles of plane P + 1, cell offsets of plane P + 3
     if (P + 1 <= zb) {
-      const uint32_t lim = min(roff[b1][ROWS], (uint32_t)CAP);
+      const uint32_t lim = min(roff[b1][ROWS], (uint32_t)CAP), t1 = here();
 #pragma unroll
       for (int s2 = 0; s2 < SPT; ++s2) {
-        const uint32_t i = tid + s2 * DEP_NT;
+        const uint32_t i = t1 + s2 * DEP_NT;
         pown[s2] = false;
         if (i < lim) load_part(source_of(b1, i, pown[s2]), pr[s2]);
       }
@@ -334,14 +443,16 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
     if (P + 3 <= zb) load_raw(cz + 3, rnext);
     // 3. sum this plane: (1 - f_z) to vertex plane cz, f_z to vertex plane cz + 1 (the first plane's
     //    lower-face sums and the last plane's upper-face sums belong to other columns and are dropped)
-    accumulate_chunk(b, 0, min(total, (uint32_t)CAP));
-    for (uint32_t c0 = CAP; c0 < total; c0 += CAP) {
+    for (uint32_t c0 = 0;;) {
+      accumulate_chunk(b, c0, min(total, c0 + (uint32_t)CAP));
+      c0 += CAP;
+      if (c0 >= total) break;
       // a crowded plane: further chunks loaded and summed in turn
       const uint32_t c1 = min(total, c0 + (uint32_t)CAP);
       __syncthreads();
 #pragma unroll
       for (int s2 = 0; s2 < SPT; ++s2) {
-        const uint32_t i = c0 + tid + s2 * DEP_NT;
+        const uint32_t i = c0 + here() + s2 * DEP_NT;
         if (i < c1) {
           bool own;
           DepPart<T> d;
@@ -350,12 +461,17 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
         }
       }
       __syncthreads();
-      accumulate_chunk(b, c0, c1);
     }
     // 4. vertex plane cz is complete: store it and move the upper-face sums down
     if (P > 0) {
       const long o = ((long)cz * n + (y0 + lvy)) * n + (x0 + lvx);
-      if (accumulate) {
+      if constexpr (VEC) {
+        // bfloat16 [vertex][16], channels 3 .. 15 zero: the closure's output gradient
+        uint4* o16 = reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(dep) + o * 16);
+        o16[0] = make_uint4((uint32_t)f2bf((float)lo4[0]) | ((uint32_t)f2bf((float)lo4[1]) << 16),
+                            (uint32_t)f2bf((float)lo4[2]), 0u, 0u);
+        o16[1] = make_uint4(0u, 0u, 0u, 0u);
+      } else if (accumulate) {
         // a further species: its sums, weighted by its particle mass over the first species', are added
 #pragma unroll
         for (int c = 0; c < N4; ++c) dep[c * n3 + o] = (T)((double)dep[c * n3 + o] + wd * lo4[c]);
@@ -392,40 +508,56 @@ __global__ __launch_bounds__(DEP_NT) void deposit_kernel(Particles<T> p, const u
   }
 }
 
-static int dep_zb(int n) { return n < DEP_ZB ? n : DEP_ZB; }
+static int dep_zb(int n) {
+  const long waves = (long)n * n / 64;  // of one layer of columns
+  int zb = n < DEP_ZB ? n : DEP_ZB;
+  while (zb > 1 && waves * (n / zb) < DEP_WAVES) zb /= 2;
+  return zb;
+}
 
 int deposit_blocks(int n) {
-  const int tx = dep_tx(n), ty = DEP_NT / tx;
+  const int tx = dep_tx(n), ty = dep_nt(n) / tx;
   return (n / tx) * (n / ty) * (n / dep_zb(n));
 }
 
-template <typename T, int TX>
-static void launch_deposit_tx(const Particles<T>& p, const uint32_t* cell_start, int n, int ncomp, bool relativistic,
-                              double a, double weight, bool accumulate, T* dep, double* esum_part, hipStream_t st) {
-  constexpr int TY = DEP_NT / TX;
+template <typename T, int NC, bool REL, int TX, int NT>
+static void launch_deposit_shape(const Particles<T>& p, const uint32_t* cell_start, int n, double a, double weight,
+                                 bool accumulate, T* dep, double* esum_part, const float* vals, hipStream_t st) {
   const int zb = dep_zb(n);
-  dim3 grid(n / TX, n / TY, n / zb);
-  const int acc = accumulate ? 1 : 0;
-  if (ncomp == 1) {
-    hipLaunchKernelGGL((deposit_kernel<T, 1, false, TX>), grid, dim3(DEP_NT), 0, st, p, cell_start, n, zb, (T)a, a,
-                       (T)weight, weight, acc, dep, (double*)nullptr);
-    return;
-  }
-  if (relativistic)
-    hipLaunchKernelGGL((deposit_kernel<T, 10, true, TX>), grid, dim3(DEP_NT), 0, st, p, cell_start, n, zb, (T)a, a,
-                       (T)weight, weight, acc, dep, esum_part);
+  hipLaunchKernelGGL((deposit_kernel<T, NC, REL, TX, NT>), dim3(n / TX, n / (NT / TX), n / zb), dim3(NT), 0, st, p,
+                     cell_start, n, zb, (T)a, a, (T)weight, weight, accumulate ? 1 : 0, dep, esum_part, vals);
+}
+
+template <typename T, int NC, bool REL>
+static void launch_deposit_nc(const Particles<T>& p, const uint32_t* cell_start, int n, double a, double weight,
+                              bool accumulate, T* dep, double* esum_part, const float* vals, hipStream_t st) {
+  if (NC > 1 && dep_nt(n) == 128)
+    launch_deposit_shape<T, NC, REL, 32, 128>(p, cell_start, n, a, weight, accumulate, dep, esum_part, vals, st);
+  else if (dep_tx(n) == 32)
+    launch_deposit_shape<T, NC, REL, 32, 256>(p, cell_start, n, a, weight, accumulate, dep, esum_part, vals, st);
   else
-    hipLaunchKernelGGL((deposit_kernel<T, 10, false, TX>), grid, dim3(DEP_NT), 0, st, p, cell_start, n, zb, (T)a, a,
-                       (T)weight, weight, acc, dep, esum_part);
+    launch_deposit_shape<T, NC, REL, 16, 256>(p, cell_start, n, a, weight, accumulate, dep, esum_part, vals, st);
 }
 
 template <typename T>
 void launch_deposit(const Particles<T>& p, const uint32_t* cell_start, int n, int ncomp, bool relativistic, double a,
                     double weight, bool accumulate, T* dep, double* esum_part, hipStream_t st) {
-  if (dep_tx(n) == 32)
-    launch_deposit_tx<T, 32>(p, cell_start, n, ncomp, relativistic, a, weight, accumulate, dep, esum_part, st);
+  if (ncomp == 1)
+    launch_deposit_nc<T, 1, false>(p, cell_start, n, a, weight, accumulate, dep, nullptr, nullptr, st);
+  else if (relativistic)
+    launch_deposit_nc<T, 10, true>(p, cell_start, n, a, weight, accumulate, dep, esum_part, nullptr, st);
   else
-    launch_deposit_tx<T, 16>(p, cell_start, n, ncomp, relativistic, a, weight, accumulate, dep, esum_part, st);
+    launch_deposit_nc<T, 10, false>(p, cell_start, n, a, weight, accumulate, dep, esum_part, nullptr, st);
+}
+
+// Adjoint of the CIC gather of three fields: the sums over particles of W vals[id] as bfloat16
+// [vertex][16], channels 3 .. 15 zero.  The store's momenta are not read, so one FP32 instance serves both
+// precisions.  (By FP32 atomics into three fields and a conversion pass: 1.85 ms at 128^3 with crowded cells.)
+void launch_deposit_vectors(const double* px, const double* py, const double* pz, const uint32_t* id,
+                            const uint32_t* cell_start, int n, const float* vals, uint16_t* out, hipStream_t st) {
+  Particles<float> p = {const_cast<double*>(px), const_cast<double*>(py), const_cast<double*>(pz), nullptr, nullptr,
+                        nullptr, const_cast<uint32_t*>(id)};
+  launch_deposit_nc<float, 3, false>(p, cell_start, n, 0.0, 1.0, false, reinterpret_cast<float*>(out), nullptr, vals, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -67,6 +67,35 @@ def test_closure_forward_and_backward_parity():
         assert ek < 2e-2
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [16, 32])
+def test_closure_backward_crowded_cells(n, precision):
+    """The adjoint of the gather (a deposit of the residuals) where cells hold up to 1500 particles; the gradient's
+    bar is that of the parity test above."""
+    from paper_2607_17929_amd import PMContext
+    from tests.test_gpu_parity import _crowded_cells
+    print("closure backward, crowded cells", n, precision, flush=True)
+    pos, u = _crowded_cells(n)
+    box = 10.0 * n
+    ctx = PMContext(n, pos.shape[0], box, physics="scalar", precision=precision, closure=True)
+    tau = opm.Background(box).tau(0.1)
+    u = 0.01 * u
+    ctx.init_particles(pos, u.astype(ctx.np_dtype), tau)
+    ctx.deposit()
+    ctx.solve_metric(0.0)
+    params = _params()
+    ctx.closure_set_params(torch.tensor(params, dtype=torch.float32))
+    ctx.closure_forward(False)
+    dpred = np.random.default_rng(4).standard_normal((pos.shape[0], 3)).astype(np.float32)
+    g = ctx.closure_backward(torch.tensor(dpred)).cpu().numpy().astype(np.float64)
+    x, _ = cnn.features(ctx.get_field("n00").astype(np.float64), ctx.get_field("phi").astype(np.float64))
+    _, acts = cnn.forward(params, x)
+    gref = cnn.backward(params, acts, cnn.gather_adjoint(dpred.astype(np.float64), pos, n))
+    offs = [0, 16 * 4 * 27 + 16, 16 * 4 * 27 + 16 + 16 * 16 * 27 + 16, cnn.N_PARAMS]
+    for k in range(3):
+        assert rel_l2(g[offs[k]:offs[k + 1]], gref[offs[k]:offs[k + 1]]) < 2e-2
+
+
 def test_closure_loss_against_oracle():
     """pm_closure_loss: the residual of the gathered output against a target, its MSE gradient and the two
     FP64 means, against the oracle's MSE on the same prediction (the GPU forms the residual in FP32)."""

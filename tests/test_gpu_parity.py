@@ -102,6 +102,37 @@ def test_deposit_parity(case, precision):
         assert rel_l2(g, ref[c]) < tol, (name, rel_l2(g, ref[c]))
 
 
+def _crowded_cells(n, seed=7):
+    """Cells of 11 .. 17, 60, 300 and 1500 particles (the deposit sums cells of 12 or more by whole waves, four
+    particles at a time, from chunks of 128 to 512) at the mesh's corners and at the deposit tiles' edges, in a
+    thin background."""
+    r = np.random.default_rng(seed)
+    cells = [(0, 0, 0), (n - 1, n - 1, n - 1), (n // 2 - 1, 3, 0), (n // 2, 4, 1), (15, 7, n - 1), (0, 8, 3),
+             (n - 1, 0, 4), (5, n - 1, 5), (6, n - 1, 5), (n // 2, n // 2, n // 2)]
+    counts = [11, 12, 13, 14, 15, 16, 17, 60, 300, 1500]
+    pos = [(np.array(c) + r.random((k, 3))) / n for c, k in zip(cells, counts)] + [r.random((n * n, 3))]
+    pos = np.concatenate(pos)
+    return pos, 0.02 * r.standard_normal(pos.shape)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [16, 32, 64])
+def test_deposit_crowded_cells(n, precision):
+    _say(f"deposit crowded n={n} {precision}")
+    pos, u = _crowded_cells(n)
+    ctx = _ctx(n, pos.shape[0], 320.0, "full", precision)
+    u = u.astype(ctx.np_dtype)
+    ctx.init_particles(pos, u, 40.0)
+    ctx.deposit()
+    ref = opm.deposit(pos, u.astype(np.float64), opm.Background(320.0).a(40.0), n)
+    # sums of up to 1500 terms: 1500 half-ulps in FP64; in FP32 the rounding of the weights and products
+    # (the bar of test_deposit_parity)
+    tol = 2e-13 if precision == "fp64" else 2e-6
+    for c, name in enumerate(["n00", "n0x", "n0y", "n0z", "nxx", "nxy", "nxz", "nyy", "nyz", "nzz"]):
+        g = ctx.get_field(name)
+        assert rel_l2(g, ref[c]) < tol, (name, rel_l2(g, ref[c]))
+
+
 # ---------------------------------------------------------------------------
 # whole steps
 # ---------------------------------------------------------------------------

@@ -139,6 +139,28 @@ __global__ void zero_kernel(unsigned char* p, size_t bytes) {
   }
 }
 
+// Device buffers to clear in one launch (a load clears up to fourteen, a few microseconds each at any size).
+struct ZeroList {
+  static constexpr int MAX = 16;
+  unsigned char* p[MAX];  // 16-byte aligned
+  size_t bytes[MAX];
+  int count = 0;
+};
+
+// grid: x = slices of a buffer, y = buffer
+__global__ __launch_bounds__(256) void zero_list_kernel(ZeroList z) {
+  unsigned char* p = z.p[blockIdx.y];
+  const size_t bytes = z.bytes[blockIdx.y];
+  const size_t stride = (size_t)gridDim.x * 256 * 16;
+  for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 16; i < bytes; i += stride) {
+    if (i + 16 <= bytes) {
+      *reinterpret_cast<uint4*>(p + i) = make_uint4(0, 0, 0, 0);
+    } else {
+      for (size_t j = i; j < bytes; ++j) p[j] = 0;
+    }
+  }
+}
+
 }  // namespace
 
 struct pm_ctx {
@@ -195,6 +217,16 @@ struct pm_ctx {
   void zero(size_t off, size_t bytes) {
     const size_t nthr = (bytes + 15) / 16;
     hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((nthr + 255) / 256)), dim3(256), 0, st, ws + off, bytes);
+  }
+  void add_zero(ZeroList& z, size_t off, size_t bytes) {
+    z.p[z.count] = ws + off;
+    z.bytes[z.count++] = bytes;
+  }
+  void zero_all(const ZeroList& z) {
+    size_t most = 0;
+    for (int i = 0; i < z.count; ++i) most = z.bytes[i] > most ? z.bytes[i] : most;
+    const size_t nb = (most + 4095) / 4096;
+    hipLaunchKernelGGL(zero_list_kernel, dim3((unsigned)(nb < 16384 ? nb : 16384), z.count), dim3(256), 0, st, z);
   }
   // any alignment, small sizes
   void zero_bytes(unsigned char* p, size_t bytes) {
@@ -278,10 +310,11 @@ void upload_tables(pm_ctx* c) {
 // one forward transform + solve + inverse transform
 // smode: the solve's mode (c->mode, or MODE_FULLP for a parabolic-B step); b_op as in SolveArgs
 // incr: solve for the increment phi_n - phi_{n-1} (phi1 = phi_{n-1}); phi_out then gets phi1 plus the
-// increment and delta_out the increment itself
+// increment and delta_out the increment itself (base in phi1's place without incr)
 template <typename T>
 void solve_pass(pm_ctx* c, const T* phi1, const T* dphi1, const T* chi1, double inv_dt, double inv_dtl, T* phi_out,
-                int tensor_op, double dtau, double hc_half, int smode, int b_op, int incr = 0, T* delta_out = nullptr) {
+                int tensor_op, double dtau, double hc_half, int smode, int b_op, int incr = 0, T* delta_out = nullptr,
+                const T* base = nullptr) {
   const Layout& L = c->L;
   const int nsrc = mode_nsrc(smode);
   const double a = c->a_of(c->tau), hc = c->hc_of(c->tau), eb = c->ebar(a);
@@ -332,7 +365,7 @@ void solve_pass(pm_ctx* c, const T* phi1, const T* dphi1, const T* chi1, double 
   fft_cols<T>(c->n, L.nhp * L.nout, spec_out, 1, true, false, tw, c->st);
   c->stage_end(PM_STAGE_FFT_Y_INV);
   c->stage_begin(PM_STAGE_FFT_X_INV);
-  fft_c2r_x<T>(c->n, L.nhp, spec_out, L.nout, outs, 1.0, tw, c->st, incr ? phi1 : nullptr, delta_out);
+  fft_c2r_x<T>(c->n, L.nhp, spec_out, L.nout, outs, 1.0, tw, c->st, incr ? phi1 : base, delta_out);
   c->stage_end(PM_STAGE_FFT_X_INV);
 }
 
@@ -353,8 +386,8 @@ pm_status do_solve(pm_ctx* c, double dtau_prev) {
     // (the parabolic B route starts from the momentum constraint's B of the second pass)
     c->zero(L.phi[sc], c->n3 * sizeof(T));
     solve_pass<T>(c, nullptr, nullptr, nullptr, 0, 0, slot(sa), 1, 0, 0, c->mode, 0);
-    solve_pass<T>(c, slot(sa), slot(sc), chi, 0, 0, slot(sb), 1, 0, 0, c->mode, 1);
-    hipMemcpyAsync(slot(sc), slot(sb), c->n3 * sizeof(T), hipMemcpyDeviceToDevice, c->st);
+    // (the zeros of slot sc as the base of an increment: phi goes to slot sb and, as it is, to slot sc)
+    solve_pass<T>(c, slot(sa), slot(sc), chi, 0, 0, slot(sb), 1, 0, 0, c->mode, 1, 0, slot(sc), slot(sc));
     c->zero(L.phi[sa], c->n3 * sizeof(T));
     c->i_phi = sb;
     c->i_prev = sc;
@@ -383,7 +416,7 @@ void sort_particles(pm_ctx* c) {
   const Layout& L = c->L;
   launch_scan(c->at<uint32_t>(L.cnt), c->at<uint32_t>(L.cell_start), c->n3, c->at<uint32_t>(L.bsum), c->st);
   launch_scatter<T>(c->parts<T>(c->cur), c->parts<T>(1 - c->cur), c->np, c->n, c->at<uint32_t>(L.rank),
-                    c->at<uint32_t>(L.cell_start), c->st);
+                    c->at<uint32_t>(L.cell_start), c->at<uint32_t>(L.cnt), c->st);
   c->cur = 1 - c->cur;
   if (c->cfg.flags & PM_FLAG_DETERMINISTIC) {
     launch_order_by_id<T>(c->parts<T>(c->cur), c->parts<T>(1 - c->cur), c->np, c->n, c->at<uint32_t>(L.cell_start),
@@ -397,7 +430,7 @@ void sort_particles2(pm_ctx* c) {
   const Layout& L = c->L;
   launch_scan(c->at<uint32_t>(L.cnt2), c->at<uint32_t>(L.cell_start2), c->n3, c->at<uint32_t>(L.bsum), c->st);
   launch_scatter<T>(c->parts2<T>(c->cur2), c->parts2<T>(1 - c->cur2), c->np2, c->n, c->at<uint32_t>(L.rank2),
-                    c->at<uint32_t>(L.cell_start2), c->st);
+                    c->at<uint32_t>(L.cell_start2), c->at<uint32_t>(L.cnt2), c->st);
   c->cur2 = 1 - c->cur2;
   if (c->cfg.flags & PM_FLAG_DETERMINISTIC) {
     launch_order_by_id<T>(c->parts2<T>(c->cur2), c->parts2<T>(1 - c->cur2), c->np2, c->n,
@@ -424,15 +457,17 @@ pm_status do_init(pm_ctx* c, const double* pos, const void* u, const uint32_t* i
     dpos = sp; du = su; dids = ids ? si : nullptr;
   }
   // clear counts, error flag, FP64 scalars, fields and tensor state
-  c->zero(L.cnt, c->n3 * 4);
-  c->zero(L.err, 64);
-  c->zero(L.scal, 8 * 8);
-  for (int i = 0; i < 3; ++i) c->zero(L.phi[i], c->n3 * c->rs);
-  if (L.chi) c->zero(L.chi, c->n3 * c->rs);
+  ZeroList z;
+  c->add_zero(z, L.cnt, c->n3 * 4);
+  c->add_zero(z, L.err, 64);
+  c->add_zero(z, L.scal, 8 * 8);
+  for (int i = 0; i < 3; ++i) c->add_zero(z, L.phi[i], c->n3 * c->rs);
+  if (L.chi) c->add_zero(z, L.chi, c->n3 * c->rs);
   for (int i = 0; i < 3; ++i)
-    if (L.b[i]) c->zero(L.b[i], c->n3 * c->rs);
-  if (L.hst) c->zero(L.hst, 4 * L.spec_comp * 2 * c->rs);
-  if (L.a2b) c->zero(L.a2b, 3 * L.spec_comp * 2 * c->rs);
+    if (L.b[i]) c->add_zero(z, L.b[i], c->n3 * c->rs);
+  if (L.hst) c->add_zero(z, L.hst, 4 * L.spec_comp * 2 * c->rs);
+  if (L.a2b) c->add_zero(z, L.a2b, 3 * L.spec_comp * 2 * c->rs);
+  c->zero_all(z);
   Particles<T> p0 = c->parts<T>(0);
   launch_ingest<T>(dpos, du, dids, np, p0, c->n, c->at<uint32_t>(L.rank), c->at<uint32_t>(L.cnt),
                    c->at<int>(L.err), c->st);

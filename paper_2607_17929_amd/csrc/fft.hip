@@ -286,8 +286,9 @@ __global__ __launch_bounds__(NT) void fft_x_c2r_kernel(const cplx<T>* spec, int 
     const long o = ((long)z * N + (y0 + r)) * N + x;
     const T v = rs[((x >> 1) * L + line) * 2 + (x & 1)] * out_scale;
     if (c == 0 && out.base0) {
+      const T b = out.base0[o];  // (may be the array the increment goes to)
       out.delta0[o] = v;
-      out.p[0][o] = out.base0[o] + v;
+      out.p[0][o] = b + v;
     } else {
       out.p[c][o] = v;
     }

@@ -138,11 +138,12 @@ struct GatherArgs {
 template <typename T>
 void launch_kick_drift(const Particles<T>& p, long np, int n, const uint32_t* cell_start, const GatherArgs<T>& g,
                        uint32_t* rank, uint32_t* cnt, int* err, hipStream_t st);
+// the two halves of the counting sort: launch_scan's counts may stay until launch_scatter (same mesh) resets them
 void launch_scan(uint32_t* cnt, uint32_t* cell_start, long ncell, uint32_t* block_sums, hipStream_t st);
 size_t scan_block_sums_count(long ncell);
 template <typename T>
 void launch_scatter(const Particles<T>& src, Particles<T> dst, long np, int nmesh, const uint32_t* rank,
-                    const uint32_t* cell_start, hipStream_t st);
+                    const uint32_t* cell_start, uint32_t* cnt, hipStream_t st);
 // move each particle of the cell-sorted src to cell_start[cell] + (particles of its cell with a smaller
 // identifier) in dst: an in-cell order that does not depend on the order of the sort's atomic ranks
 template <typename T>

@@ -821,7 +821,7 @@ void launch_kick_drift(const Particles<T>& p, long np, int n, const uint32_t* ce
 
 // ---------------------------------------------------------------------------
 // exclusive scan of the per-cell counts -> cell_start (n^3 + 1 entries);
-// the counts are reset to zero for the next histogram.
+// the counts are reset to zero for the next histogram (by the scan or by the scatter that follows it).
 // ---------------------------------------------------------------------------
 constexpr int SCAN_NT = 256, SCAN_PER = 16, SCAN_CHUNK = SCAN_NT * SCAN_PER;
 
@@ -873,35 +873,65 @@ __global__ __launch_bounds__(1024) void scan_blocks_kernel(uint32_t* bsum, long 
   }
 }
 
+// Where the chunk's offset comes from: the scanned block sums, the block sums before it (added up here, one launch
+// less), or the counts before it themselves (two launches less; the counts are then reset by the scatter, after
+// every chunk has read them).
+enum { SCAN_OFFSETS = 0, SCAN_SUMS = 1, SCAN_COUNTS = 2 };
+
 // exclusive scan of one chunk: striped coalesced loads into LDS, per-thread scan of 16
 // consecutive values (padded LDS rows), block scan of the thread totals, striped stores
+template <int FROM>
 __global__ __launch_bounds__(SCAN_NT) void scan_apply_kernel(uint32_t* cnt, long ncell, const uint32_t* boff,
                                                              uint32_t* cell_start) {
   constexpr int PAD = SCAN_PER + 1;
   __shared__ uint32_t buf[SCAN_NT * PAD];
-  __shared__ uint32_t part[SCAN_NT];
+  __shared__ uint32_t part[SCAN_NT / 64], before[SCAN_NT / 64];
   const long base = (long)blockIdx.x * SCAN_CHUNK;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t pre = 0;
+  if constexpr (FROM == SCAN_SUMS) {
+    for (int i = t; i < (int)blockIdx.x; i += SCAN_NT) pre += boff[i];
+  } else if constexpr (FROM == SCAN_COUNTS) {
+    const uint4* c4 = reinterpret_cast<const uint4*>(cnt);  // whole chunks, 16-byte aligned
+#pragma unroll 4
+    for (int i = t; i < (int)base / 4; i += SCAN_NT) {
+      const uint4 v = c4[i];
+      pre += v.x + v.y + v.z + v.w;
+    }
+  }
 #pragma unroll
   for (int j = 0; j < SCAN_PER; ++j) {
     const int q = t + j * SCAN_NT;  // element of the chunk
     const long i = base + q;
     buf[(q / SCAN_PER) * PAD + q % SCAN_PER] = (i < ncell) ? cnt[i] : 0u;
-    if (i < ncell) cnt[i] = 0u;
+    if (FROM != SCAN_COUNTS && i < ncell) cnt[i] = 0u;
   }
   __syncthreads();
   uint32_t s = 0;
 #pragma unroll
   for (int j = 0; j < SCAN_PER; ++j) s += buf[t * PAD + j];
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < SCAN_NT; off <<= 1) {
-    const uint32_t v = (t >= off) ? part[t - off] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
+  // inclusive scan of the thread totals within the wave, then the waves' totals in order
+  uint32_t inc = s;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t v = __shfl_up(inc, d);
+    if (lane >= d) inc += v;
   }
-  uint32_t run = boff[blockIdx.x] + ((t == 0) ? 0u : part[t - 1]);
+  if (lane == 63) part[wave] = inc;
+  if constexpr (FROM != SCAN_OFFSETS) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) pre += __shfl_down(pre, d);
+    if (lane == 0) before[wave] = pre;
+  }
+  __syncthreads();
+  uint32_t run = inc - s, total = 0, first = FROM == SCAN_OFFSETS ? boff[blockIdx.x] : 0u;
+#pragma unroll
+  for (int w = 0; w < SCAN_NT / 64; ++w) {
+    if (w < wave) run += part[w];
+    total += part[w];
+    if (FROM != SCAN_OFFSETS) first += before[w];
+  }
+  run += first;
 #pragma unroll
   for (int j = 0; j < SCAN_PER; ++j) {
     const uint32_t v = buf[t * PAD + j];
@@ -915,17 +945,28 @@ __global__ __launch_bounds__(SCAN_NT) void scan_apply_kernel(uint32_t* cnt, long
     const long i = base + q;
     if (i < ncell) cell_start[i] = buf[(q / SCAN_PER) * PAD + q % SCAN_PER];
   }
-  if (base + SCAN_CHUNK >= ncell && t == SCAN_NT - 1) {
-    // the last block also writes the total at cell_start[ncell]
-    cell_start[ncell] = boff[blockIdx.x] + part[SCAN_NT - 1];
-  }
+  // the last block also writes the total at cell_start[ncell]
+  if (base + SCAN_CHUNK >= ncell && t == 0) cell_start[ncell] = first + total;
 }
+
+// The lines of the rule: 32^3 (8 chunks, one launch of 6 us for three of 6 + 3 + 6), 256^3 (4096 chunks: adding up
+// the block sums costs 2 us, the launch between cost 4); at 512^3 every chunk would read 128 KB of block sums.
+static bool scan_from_counts(long ncell) { return scan_block_sums_count(ncell) <= 8; }
 
 void launch_scan(uint32_t* cnt, uint32_t* cell_start, long ncell, uint32_t* block_sums, hipStream_t st) {
   const long nb = (long)scan_block_sums_count(ncell);
-  hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nb), dim3(SCAN_NT), 0, st, cnt, ncell, block_sums);
+  const dim3 grid((unsigned)nb), block(SCAN_NT);
+  if (scan_from_counts(ncell)) {
+    hipLaunchKernelGGL(scan_apply_kernel<SCAN_COUNTS>, grid, block, 0, st, cnt, ncell, block_sums, cell_start);
+    return;
+  }
+  hipLaunchKernelGGL(scan_reduce_kernel, grid, block, 0, st, cnt, ncell, block_sums);
+  if (nb <= 4096) {
+    hipLaunchKernelGGL(scan_apply_kernel<SCAN_SUMS>, grid, block, 0, st, cnt, ncell, block_sums, cell_start);
+    return;
+  }
   hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, st, block_sums, nb);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(SCAN_NT), 0, st, cnt, ncell, block_sums, cell_start);
+  hipLaunchKernelGGL(scan_apply_kernel<SCAN_OFFSETS>, grid, block, 0, st, cnt, ncell, block_sums, cell_start);
 }
 
 // ---------------------------------------------------------------------------
@@ -937,7 +978,10 @@ constexpr int SC_PER = 2;  // particles per thread: independent load chains in f
 template <typename T>
 __global__ __launch_bounds__(256) void scatter_kernel(Particles<T> s, Particles<T> d, long np, int nmesh,
                                                       const uint32_t* __restrict__ rank,
-                                                      const uint32_t* __restrict__ cell_start) {
+                                                      const uint32_t* __restrict__ cell_start, uint32_t* cnt,
+                                                      int nreset) {
+  // counts left standing by the scan
+  for (int c = (int)(blockIdx.x * 256 + threadIdx.x); c < nreset; c += (int)(gridDim.x * 256)) cnt[c] = 0u;
   const long base = (long)xcd_remap(blockIdx.x, gridDim.x) * (256 * SC_PER) + threadIdx.x;
   // every read that does not depend on the destination is issued first
   uint32_t r[SC_PER], id[SC_PER];
@@ -969,10 +1013,11 @@ __global__ __launch_bounds__(256) void scatter_kernel(Particles<T> s, Particles<
 
 template <typename T>
 void launch_scatter(const Particles<T>& src, Particles<T> dst, long np, int nmesh, const uint32_t* rank,
-                    const uint32_t* cell_start, hipStream_t st) {
-  const long per_block = 256 * SC_PER;
+                    const uint32_t* cell_start, uint32_t* cnt, hipStream_t st) {
+  const long per_block = 256 * SC_PER, ncell = (long)nmesh * nmesh * nmesh;
+  const int nreset = scan_from_counts(ncell) ? (int)ncell : 0;
   hipLaunchKernelGGL((scatter_kernel<T>), dim3((unsigned)((np + per_block - 1) / per_block)), dim3(256), 0, st, src, dst,
-                     np, nmesh, rank, cell_start);
+                     np, nmesh, rank, cell_start, cnt, nreset);
 }
 
 // ---------------------------------------------------------------------------
@@ -1101,7 +1146,7 @@ void launch_copy_unpad(const cplx<T>* spec, int n, int nhp, cplx<T>* out, bool t
   template void launch_kick_drift<T>(const Particles<T>&, long, int, const uint32_t*, const GatherArgs<T>&, uint32_t*, \
                                      uint32_t*, int*, hipStream_t);                                                    \
   template void launch_scatter<T>(const Particles<T>&, Particles<T>, long, int, const uint32_t*, const uint32_t*,      \
-                                  hipStream_t);                                                                        \
+                                  uint32_t*, hipStream_t);                                                                        \
   template void launch_export<T>(const Particles<T>&, long, double*, T*, uint32_t*, hipStream_t);                      \
   template void launch_check_store<T>(const Particles<T>&, long, int, const uint32_t*, int*, hipStream_t);            \
   template void launch_order_by_id<T>(const Particles<T>&, Particles<T>, long, int, const uint32_t*, hipStream_t);     \

@@ -116,7 +116,7 @@ def _crowded_cells(n, seed=7):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("n", [16, 32, 64])
+@pytest.mark.parametrize("n", [16, 32, 64, 128])  # (the sort's scan of the counts takes 1, 8, 64 and 512 chunks)
 def test_deposit_crowded_cells(n, precision):
     _say(f"deposit crowded n={n} {precision}")
     pos, u = _crowded_cells(n)

@@ -98,7 +98,7 @@ Layout make_layout(const pm_config& c) {
     L.cl_wf = take(3 * 27 * 256 * 2);
     L.cl_wb = take(3 * 27 * 256 * 2);
     L.cl_bias = take(3 * 16 * 4);
-    L.cl_scal = take(2048 * 8);  // [0..528) features, [4..6) loss, [1024..2048) loss partials
+    L.cl_scal = take(6144 * 8);  // [0] sum of n00, [1] rms, [4..6) loss, [1024..2048) loss and [2048..6144) feature partials
     // training buffers only on meshes up to 256^3 (the back-propagated activations grow with n^3)
     L.cl_train = n <= 256;
     if (L.cl_train) {
@@ -510,13 +510,10 @@ void closure_forward_impl(pm_ctx* c, bool scaled) {
   const Layout& L = c->L;
   double* cs = c->at<double>(L.cl_scal);
   float* rms = reinterpret_cast<float*>(cs + 1);
-  // FP64 sum of n00 into cs[0], partials in cs[8..]
-  if (c->cfg.precision == PM_FP64) launch_sum_f64(c->at<double>(L.dep), c->n3, cs, c->st);
-  else launch_sum_as_f64(c->at<float>(L.dep), c->n3, cs, c->st);
   uint16_t* a0 = c->at<uint16_t>(L.cl_act[0]);
   uint16_t* a1 = c->at<uint16_t>(L.cl_act[1]);
   uint16_t* a2 = c->at<uint16_t>(L.cl_act[2]);
-  closure_features<T>(c->at<T>(L.dep), c->at<T>(L.phi[c->i_phi]), c->n, cs, cs + 16, rms, a0, c->st);
+  closure_features<T>(c->at<T>(L.dep), c->at<T>(L.phi[c->i_phi]), c->n, cs, cs + 2048, rms, a0, c->st);
   const uint16_t* wf = c->at<uint16_t>(L.cl_wf);
   const float* bias = c->at<float>(L.cl_bias);
   closure_conv(a0, wf, bias, c->n, 0, a1, nullptr, nullptr, c->st);

@@ -34,72 +34,98 @@ __device__ __forceinline__ int tap_dz(int t) { return t / 9 - 1; }
 __device__ __forceinline__ int tap_dy(int t) { return (t / 3) % 3 - 1; }
 __device__ __forceinline__ int tap_dx(int t) { return t % 3 - 1; }
 
-// Load the input block plus margin into LDS: [hz][hy][hx][16] bfloat16, 16-byte chunks.
-__device__ __forceinline__ void load_halo(const uint16_t* __restrict__ in, int n, int x0, int y0, int z0,
-                                          uint4* __restrict__ lds) {
-  const int m = n - 1;
-  const long nn = (long)n * n;
-  for (int q = threadIdx.x; q < CV_HP * 2; q += CV_NT) {
-    const int pt = q >> 1, half = q & 1;
-    const int hx = pt % CV_HX, hy = (pt / CV_HX) % CV_HY, hz = pt / (CV_HX * CV_HY);
-    const long g = (long)((z0 - 1 + hz) & m) * nn + (long)((y0 - 1 + hy) & m) * n + ((x0 - 1 + hx) & m);
-    lds[q] = reinterpret_cast<const uint4*>(in + g * 16)[half];
-  }
+// 16 bytes a lane from global memory straight into LDS: lane l's go to lds + l (lds is the wave's, not the lane's);
+// the wave's s_waitcnt vmcnt(0) tells that they are there
+__device__ __forceinline__ void load_lds16(const uint16_t* g, uint4* lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
 
 // mode: 0 = relu(conv + bias) -> bf16 [p][16]; 1 = (conv + bias)[0..2] * scale -> FP32 SoA [3][n^3];
 //       2 = conv * (mask > 0) -> bf16 [p][16] (input gradient through a ReLU)
+//
+// The input block plus margin goes from global memory straight into LDS ([hz][hy][hx][16], 16 bytes a lane, all nine
+// loads of a wave in flight; through registers one after the other they were most of the kernel's time).  The weights
+// are the product's rows and the points its columns, so that a lane ends with 4 consecutive channels of one point
+// and a row of 16 points is stored as 512 consecutive bytes.  A K-step holds two consecutive taps, the second in
+// the upper lanes: it lies one point, one row or one plane further, so three lane addresses and immediate offsets
+// reach all 27 taps of every row.
 template <int MODE>
 __global__ __launch_bounds__(CV_NT) void conv16_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
                                                        const float* __restrict__ bias, int n, void* out,
                                                        const uint16_t* __restrict__ mask, const float* scale_ptr) {
   __shared__ uint4 tile[CV_HP * 2];
   const int x0 = blockIdx.x * CV_TX, y0 = blockIdx.y * CV_TY, z0 = blockIdx.z * CV_TZ;
-  load_halo(in, n, x0, y0, z0, tile);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long nn = (long)n * n;
+  const int m = n - 1, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  constexpr int NLD = (CV_HP * 2 + CV_NT - 1) / CV_NT;
+#pragma unroll
+  for (int k = 0; k < NLD; ++k) {
+    const int q0 = (wave + k * (CV_NT / 64)) * 64, q = q0 + lane;
+    if (q < CV_HP * 2) {
+      const int pt = q >> 1, half = q & 1;
+      const int hx = pt % CV_HX, hy = (pt / CV_HX) % CV_HY, hz = pt / (CV_HX * CV_HY);
+      const long g = (long)((z0 - 1 + hz) & m) * nn + (long)((y0 - 1 + hy) & m) * n + ((x0 - 1 + hx) & m);
+      load_lds16(in + g * 16 + half * 8, tile + q0);
+    }
+  }
   const int col = lane & 15, grp = lane >> 4;
-  // B fragments (weights, [tap][out][in] bfloat16) for the 14 K-steps, kept in registers
-  v8bf bfrag[CV_KSTEPS];
+  // weight fragments ([tap][out][in] bfloat16, lane: out channel col, 8 input channels) of the 14 K-steps in registers
+  v8bf wfrag[CV_KSTEPS];
 #pragma unroll
   for (int s = 0; s < CV_KSTEPS; ++s) {
     const int t = 2 * s + (grp >> 1);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (t < 27) v = *reinterpret_cast<const uint4*>(w + ((t * 16 + col) * 16 + 8 * (grp & 1)));
-    bfrag[s] = __builtin_bit_cast(v8bf, v);
+    uint4 u = make_uint4(0, 0, 0, 0);
+    if (t < 27) u = *reinterpret_cast<const uint4*>(w + ((t * 16 + col) * 16 + 8 * (grp & 1)));
+    wfrag[s] = __builtin_bit_cast(v8bf, u);
   }
-  __syncthreads();
-  const long n3 = (long)n * n * n;
   const float scale = (MODE == 1 && scale_ptr) ? scale_ptr[0] : 1.0f;
-  const float bco = bias ? bias[col] : 0.0f;
-  // each wave computes 8 rows of 16 points
-  for (int r = wave; r < CV_TY * CV_TZ; r += CV_NT / 64) {
-    const int ly = r % CV_TY, lz = r / CV_TY;
+  float bco[4] = {0.f, 0.f, 0.f, 0.f};
+  if (bias) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bco[j] = bias[4 * grp + j];
+  }
+  const long n3 = nn * n;
+  // each wave computes 8 rows of 16 points (one plane of the block)
+  static_assert(CV_NT / 64 == CV_TZ, "one wave per plane");
+  const int lz = wave;
+  const int up = grp >> 1;
+  const uint4* b0 = tile + (lz * CV_HY * CV_HX + col) * 2 + (grp & 1);  // point col of the plane's first row
+  const uint4* b1 = b0 + up * 2;                                        // the second tap at the next point,
+  const uint4* b2 = b0 + up * ((CV_HX - 2) * 2);                        // in the next row,
+  const uint4* b3 = b0 + up * ((CV_HY * CV_HX - 2 * CV_HX - 2) * 2);    // in the next plane
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the block is in LDS
+  __syncthreads();
+#pragma unroll
+  for (int ly = 0; ly < CV_TY; ++ly) {
     v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < CV_KSTEPS; ++s) {
-      const int t = 2 * s + (grp >> 1);
-      uint4 av = make_uint4(0, 0, 0, 0);
-      if (t < 27) {
-        // A: point x = col of this row, shifted by the tap; 8 input channels
-        const int hx = col + 1 + tap_dx(t), hy = ly + 1 + tap_dy(t), hz = lz + 1 + tap_dz(t);
-        av = tile[((hz * CV_HY + hy) * CV_HX + hx) * 2 + (grp & 1)];
-      }
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av), bfrag[s], acc, 0, 0, 0);
+      // (the 28th tap has weight zero: its lanes read the 27th's values)
+      const int t = 2 * s, o = ((t / 9 * CV_HY + (t / 3) % 3 + ly) * CV_HX + t % 3) * 2;
+      const uint4* b = (s == CV_KSTEPS - 1) ? b0 : (t % 3 != 2 ? b1 : ((t / 3) % 3 != 2 ? b2 : b3));
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfrag[s], __builtin_bit_cast(v8bf, b[o]), acc, 0, 0, 0);
     }
-    // D: lane holds rows (points) 4*grp + j of column (output channel) col
+    // D: lane holds output channels 4 grp + j of point col
+    const long p = ((long)(z0 + lz) * n + (y0 + ly)) * n + (x0 + col);
+    if constexpr (MODE == 1) {
+      if (grp == 0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int px = 4 * grp + j;
-      const long p = ((long)(z0 + lz) * n + (y0 + ly)) * n + (x0 + px);
-      const float v = acc[j] + bco;
-      if constexpr (MODE == 0) {
-        reinterpret_cast<uint16_t*>(out)[p * 16 + col] = f2bf(fmaxf(v, 0.0f));
-      } else if constexpr (MODE == 1) {
-        if (col < 3) reinterpret_cast<float*>(out)[col * n3 + p] = v * scale;
-      } else {
-        const bool on = bf2f(mask[p * 16 + col]) > 0.0f;
-        reinterpret_cast<uint16_t*>(out)[p * 16 + col] = f2bf(on ? acc[j] : 0.0f);
+        for (int j = 0; j < 3; ++j) reinterpret_cast<float*>(out)[j * n3 + p] = (acc[j] + bco[j]) * scale;
       }
+    } else {
+      uint16_t r[4];
+      if constexpr (MODE == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[j] = f2bf(fmaxf(acc[j] + bco[j], 0.0f));
+      } else {
+        const uint2 mk = *reinterpret_cast<const uint2*>(mask + p * 16 + 4 * grp);
+        const uint16_t mw[4] = {(uint16_t)mk.x, (uint16_t)(mk.x >> 16), (uint16_t)mk.y, (uint16_t)(mk.y >> 16)};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[j] = f2bf(bf2f(mw[j]) > 0.0f ? acc[j] : 0.0f);
+      }
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + p * 16 + 4 * grp) =
+          make_uint2((uint32_t)r[0] | ((uint32_t)r[1] << 16), (uint32_t)r[2] | ((uint32_t)r[3] << 16));
     }
   }
 }
@@ -107,24 +133,34 @@ __global__ __launch_bounds__(CV_NT) void conv16_kernel(const uint16_t* __restric
 // Weight gradient of one layer on the matrix cores: for each tap t,
 // dW_t[co][ci] = sum_p dy[p][co] x[p + d_t][ci] is a 16 x 16 GEMM with K running over the
 // points.  One MFMA takes 32 points (two x-rows of a 16 x 8 x 4 tile): A[co][k] = dy[p_k][co],
-// B[k][ci] = x[p_k + d_t][ci].  Both operands need 8 consecutive points per lane for one
-// channel, so the tile is transposed into LDS channel-major ([ci][hz][hy][hx] with rows of
-// WG_ROW elements, [co][row][lx] for dy); the x-shift of a tap is then a funnel shift of
-// two aligned words.  Wave w owns taps w, w + 4, ..., and wave 3's spare slot accumulates the
+// B[k][ci] = x[p_k + d_t][ci].  Both operands need 8 consecutive points per lane for one channel, the transpose of
+// the [point][16] layout in memory: the tile goes straight into LDS as it is (16 bytes a lane) and is transposed by
+// the reads (ds_read_b64_tr_b16: of the 4 points x 16 channels that the addresses of 16 lanes cover, lane i gets
+// channel i of the 4 points), so that a tap's shift is an address.  (Transposed into LDS by 2-byte stores the kernel
+// took 137 us at 128^3 and 1.04 ms at 256^3.)  Wave w owns taps w, w + 4, ..., and wave 3's spare slot accumulates the
 // bias gradient (B = ones).  A workgroup walks tiles blockIdx.x, + gridDim.x, ... and writes
 // one FP32 partial; the partials are summed in a fixed order in FP64.
-constexpr int WG_ROW = 24;                              // LDS row: 18 halo points + pad, 16-byte aligned
-constexpr int WG_CI = CV_HZ * CV_HY * WG_ROW + 8;       // channel stride (pad spreads the banks)
-constexpr int WG_CO = CV_TX * CV_TY * CV_TZ + 8;        // dy channel stride
 constexpr int WG_PART = 27 * 256 + 16;                  // one partial: [t][co][ci] then the bias [co]
-constexpr int WG_GRID = 512;                            // workgroups (partials) at most
+constexpr int WG_GRID = 768;                            // workgroups (partials) at most: 3 a CU (51 KB of LDS each)
+
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef short v8s __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+
+// channel lane % 16 of the 8 points from byte offset `at` of p on (this lane's part of the first four; the next four
+// are 128 bytes further)
+__device__ __forceinline__ v8bf read_points8(const uint8_t* p, int at) {
+  const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + at));
+  const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + at + 128));
+  return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 
 __global__ __launch_bounds__(CV_NT) void conv16_wgrad_kernel(const uint16_t* __restrict__ x,
                                                              const uint16_t* __restrict__ dy, int n, long ntiles,
                                                              float* __restrict__ part) {
-  __shared__ __align__(16) uint16_t xt[16 * WG_CI];
-  __shared__ __align__(16) uint16_t dyt[16 * WG_CO];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ uint4 xt[CV_HP * 2];                  // [hz][hy][hx][16]
+  __shared__ uint4 dyt[CV_TX * CV_TY * CV_TZ * 2]; // [lz][ly][lx][16]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
   const int ntx = n / CV_TX, nty = n / CV_TY;
   const int m = n - 1;
@@ -133,58 +169,51 @@ __global__ __launch_bounds__(CV_NT) void conv16_wgrad_kernel(const uint16_t* __r
 #pragma unroll
   for (int j = 0; j < 7; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
   const v8bf ones = __builtin_bit_cast(v8bf, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+  // lane's read addresses: points 8 (grp & 1) + (lane % 16) / 4 of x-row grp / 2 of a pair, 4 channels each
+  const int px = 8 * (grp & 1) + (col >> 2), pr = grp >> 1;
+  const uint8_t* ab = reinterpret_cast<const uint8_t*>(dyt) + (pr * CV_TX + px) * 32 + (col & 3) * 8;
+  const uint8_t* xb[7];
+#pragma unroll
+  for (int j = 0; j < 7; ++j) {
+    const int t = min(wave + 4 * j, 26);
+    const int off = ((1 + tap_dz(t)) * CV_HY + 1 + tap_dy(t)) * CV_HX + 1 + tap_dx(t);
+    xb[j] = reinterpret_cast<const uint8_t*>(xt) + (off + pr * CV_HX + px) * 32 + (col & 3) * 8;
+  }
   for (long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int x0 = (int)(tile % ntx) * CV_TX, y0 = (int)((tile / ntx) % nty) * CV_TY;
     const int z0 = (int)(tile / ((long)ntx * nty)) * CV_TZ;
     __syncthreads();  // the previous tile's operands are consumed
-    for (int q = threadIdx.x; q < CV_HP * 2; q += CV_NT) {
-      const int pt = q >> 1, half = q & 1;
-      const int hx = pt % CV_HX, hy = (pt / CV_HX) % CV_HY, hz = pt / (CV_HX * CV_HY);
-      const long g = (long)((z0 - 1 + hz) & m) * nn + (long)((y0 - 1 + hy) & m) * n + ((x0 - 1 + hx) & m);
-      const uint4 v = reinterpret_cast<const uint4*>(x + g * 16)[half];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-      uint16_t* d = xt + (8 * half) * WG_CI + (hz * CV_HY + hy) * WG_ROW + hx;
+    constexpr int NX = (CV_HP * 2 + CV_NT - 1) / CV_NT, ND = CV_TX * CV_TY * CV_TZ * 2 / CV_NT;
 #pragma unroll
-      for (int c = 0; c < 8; ++c) d[c * WG_CI] = (uint16_t)(w[c >> 1] >> (16 * (c & 1)));
+    for (int k = 0; k < NX; ++k) {
+      const int q0 = (wave + k * (CV_NT / 64)) * 64, q = q0 + lane;
+      if (q < CV_HP * 2) {
+        const int pt = q >> 1, half = q & 1;
+        const int hx = pt % CV_HX, hy = (pt / CV_HX) % CV_HY, hz = pt / (CV_HX * CV_HY);
+        const long g = (long)((z0 - 1 + hz) & m) * nn + (long)((y0 - 1 + hy) & m) * n + ((x0 - 1 + hx) & m);
+        load_lds16(x + g * 16 + half * 8, xt + q0);
+      }
     }
-    for (int q = threadIdx.x; q < CV_TX * CV_TY * CV_TZ * 2; q += CV_NT) {
+#pragma unroll
+    for (int k = 0; k < ND; ++k) {
+      const int q0 = (wave + k * (CV_NT / 64)) * 64, q = q0 + lane;
       const int pt = q >> 1, half = q & 1;
       const int lx = pt % CV_TX, row = pt / CV_TX;  // row = ly + 8 lz
       const long g = ((long)(z0 + row / CV_TY) * n + (y0 + row % CV_TY)) * n + (x0 + lx);
-      const uint4 v = reinterpret_cast<const uint4*>(dy + g * 16)[half];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-      uint16_t* d = dyt + (8 * half) * WG_CO + pt;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) d[c * WG_CO] = (uint16_t)(w[c >> 1] >> (16 * (c & 1)));
+      load_lds16(dy + g * 16 + half * 8, dyt + q0);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the tile is in LDS
     __syncthreads();
-    // lane (col, grp) of K-step s: points lx = 8 (grp & 1) + e, e < 8, of row 2 s + (grp >> 1)
-    const int xb = 8 * (grp & 1);
+    // K-step s: points lx = 8 (grp & 1) + e, e < 8, of row 2 s + (grp >> 1)
+#pragma unroll
     for (int s = 0; s < CV_TY * CV_TZ / 2; ++s) {
-      const int row = 2 * s + (grp >> 1);
-      const int ly = row % CV_TY, lz = row / CV_TY;
-      const v8bf a = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4*>(dyt + col * WG_CO + row * CV_TX + xb));
+      const v8bf a = read_points8(ab, s * 2 * CV_TX * 32);
+      const int xo = ((2 * s / CV_TY) * CV_HY + 2 * s % CV_TY) * CV_HX * 32;
 #pragma unroll
       for (int j = 0; j < 7; ++j) {
-        const int t = wave + 4 * j;
-        if (t < 27) {
-          const int hz = lz + 1 + tap_dz(t), hy = ly + 1 + tap_dy(t), dx = tap_dx(t);
-          const uint16_t* r = xt + col * WG_CI + (hz * CV_HY + hy) * WG_ROW + xb;
-          // halo points xb + 1 + dx + e: from the aligned words at xb .. xb + 9
-          const uint4 w = *reinterpret_cast<const uint4*>(r);
-          uint4 b;
-          if (dx < 0) {
-            b = w;
-          } else {
-            const uint32_t w4 = *reinterpret_cast<const uint32_t*>(r + 8);
-            if (dx > 0) b = make_uint4(w.y, w.z, w.w, w4);
-            else b = make_uint4(__builtin_amdgcn_alignbit(w.y, w.x, 16), __builtin_amdgcn_alignbit(w.z, w.y, 16),
-                                __builtin_amdgcn_alignbit(w.w, w.z, 16), __builtin_amdgcn_alignbit(w4, w.w, 16));
-          }
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(v8bf, b), acc[j], 0, 0, 0);
-        } else {
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[j], 0, 0, 0);
-        }
+        const bool bias_slot = j == 6 && wave == 3;
+        const v8bf b = bias_slot ? ones : read_points8(xb[j], xo);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[j], 0, 0, 0);
       }
     }
   }
@@ -203,21 +232,27 @@ __global__ __launch_bounds__(CV_NT) void conv16_wgrad_kernel(const uint16_t* __r
 }
 
 // sum the partials in a fixed order (FP64) and scatter into the flat parameter-gradient layout
-// W[co][ci][27] b[co] of layer (ci_n -> co_n) at offset off; 64 entries per workgroup, each wave
-// adds a contiguous quarter of the partials and the quarters are combined in order
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ part, int nblk, int ci_n, int co_n,
-                                                           float* __restrict__ grad, long off) {
-  __shared__ double q[4][64];
+// W[co][ci][27] b[co] of layer (ci_n -> co_n) at offset off; 64 entries per workgroup, each of 16 waves
+// adds a contiguous sixteenth of the partials (four sixteenths took 34 us, a latency chain of 128 loads) and
+// the parts are combined in order
+constexpr int WR_PARTS = 16;
+__global__ __launch_bounds__(64 * WR_PARTS) void wgrad_reduce_kernel(const float* __restrict__ part, int nblk, int ci_n,
+                                                                     int co_n, float* __restrict__ grad, long off) {
+  __shared__ double q[WR_PARTS][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + lane;
-  const int lo = wave * nblk / 4, hi = (wave + 1) * nblk / 4;
+  const int lo = wave * nblk / WR_PARTS, hi = (wave + 1) * nblk / WR_PARTS;
   double s = 0.0;
-  if (e < WG_PART)
+  if (e < WG_PART) {
+#pragma unroll 8
     for (int b = lo; b < hi; ++b) s += (double)part[(long)b * WG_PART + e];
+  }
   q[wave][lane] = s;
   __syncthreads();
   if (wave != 0 || e >= WG_PART) return;
-  s = ((q[0][lane] + q[1][lane]) + q[2][lane]) + q[3][lane];
+  s = q[0][lane];
+#pragma unroll
+  for (int w = 1; w < WR_PARTS; ++w) s += q[w][lane];
   if (e < 27 * 256) {
     const int t = e / 256, co = (e / 16) % 16, ci = e % 16;
     if (co < co_n && ci < ci_n) grad[off + ((long)co * ci_n + ci) * 27 + t] = (float)s;
@@ -269,66 +304,104 @@ __global__ __launch_bounds__(256) void adam_kernel(float* p, float* m, float* v,
 // ---------------------------------------------------------------------------
 // inputs: channel 0 = sign(delta) log(1 + |delta|), channels 1..3 = grad phi / rms|grad phi|
 // ---------------------------------------------------------------------------
+// One pass over both inputs: FP64 partials of |grad phi|^2 (part[0 .. blocks)) and of n00 (part[blocks .. 2 blocks)).
+// Four consecutive x a thread; a grid of whole rounds of the chip in place of 512 workgroups with two 64-bit
+// divisions a point (100 us, and 55 us for the separate sum of n00, at 256^3).
+constexpr int FEAT_BLOCKS = 2048;
 template <typename T>
-__global__ __launch_bounds__(256) void gradsq_partial_kernel(const T* __restrict__ phi, int n, double* part) {
-  __shared__ double red[256];
-  const long n3 = (long)n * n * n;
-  const int m = n - 1;
-  double acc = 0.0;
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n3; i += (long)gridDim.x * 256) {
-    const int x = (int)(i % n), y = (int)((i / n) % n), z = (int)(i / ((long)n * n));
-    const long nn = (long)n * n;
-    const double hn = 0.5 * n;
-    const double gx = ((double)phi[z * nn + y * n + ((x + 1) & m)] - (double)phi[z * nn + y * n + ((x - 1) & m)]) * hn;
-    const double gy = ((double)phi[z * nn + ((y + 1) & m) * n + x] - (double)phi[z * nn + ((y - 1) & m) * n + x]) * hn;
-    const double gz = ((double)phi[((z + 1) & m) * nn + y * n + x] - (double)phi[((z - 1) & m) * nn + y * n + x]) * hn;
-    acc += gx * gx + gy * gy + gz * gz;
+__global__ __launch_bounds__(256) void field_sums_kernel(const T* __restrict__ n00, const T* __restrict__ phi, int lg,
+                                                         double* part) {
+  __shared__ double red[2][4];
+  const int n = 1 << lg, m = n - 1;
+  const long nn = 1L << (2 * lg), n4 = nn << lg >> 2;
+  const double hn = 0.5 * n;
+  double g2 = 0.0, s0 = 0.0;
+  for (long q = (long)blockIdx.x * 256 + threadIdx.x; q < n4; q += (long)gridDim.x * 256) {
+    const long i = q * 4;
+    const int x = (int)i & m, y = (int)(i >> lg) & m, z = (int)(i >> (2 * lg));
+    const long row = i - x;
+    const V4<T> c = *reinterpret_cast<const V4<T>*>(phi + i);
+    const T xm = phi[row + ((x - 1) & m)], xp = phi[row + ((x + 4) & m)];
+    const long rz = (long)z << (2 * lg), ry = (long)y << lg;
+    const V4<T> yp = *reinterpret_cast<const V4<T>*>(phi + rz + ((long)((y + 1) & m) << lg) + x);
+    const V4<T> ym = *reinterpret_cast<const V4<T>*>(phi + rz + ((long)((y - 1) & m) << lg) + x);
+    const V4<T> zp = *reinterpret_cast<const V4<T>*>(phi + ((long)((z + 1) & m) << (2 * lg)) + ry + x);
+    const V4<T> zm = *reinterpret_cast<const V4<T>*>(phi + ((long)((z - 1) & m) << (2 * lg)) + ry + x);
+    const V4<T> d = *reinterpret_cast<const V4<T>*>(n00 + i);
+    auto add = [&](T a, T b) {
+      const double g = ((double)a - (double)b) * hn;
+      g2 += g * g;
+    };
+    add(c.y, xm); add(c.z, c.x); add(c.w, c.y); add(xp, c.z);
+    add(yp.x, ym.x); add(yp.y, ym.y); add(yp.z, ym.z); add(yp.w, ym.w);
+    add(zp.x, zm.x); add(zp.y, zm.y); add(zp.z, zm.z); add(zp.w, zm.w);
+    s0 += ((double)d.x + (double)d.y) + ((double)d.z + (double)d.w);
   }
-  red[threadIdx.x] = acc;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    g2 += __shfl_down(g2, d);
+    s0 += __shfl_down(s0, d);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = g2;
+    red[1][threadIdx.x >> 6] = s0;
+  }
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  if (threadIdx.x < 2) {
+    const double* r = red[threadIdx.x];
+    part[threadIdx.x * gridDim.x + blockIdx.x] = ((r[0] + r[1]) + r[2]) + r[3];
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// scal[0] <- rms |grad phi| (FP32), from the partials
-__global__ void gradsq_final_kernel(const double* part, int nb, long n3, float* rms) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < nb; i += 256) s += part[i];
-  red[threadIdx.x] = s;
+// rms |grad phi| (FP32) and the sum of n00 from the partials
+__global__ __launch_bounds__(256) void field_sums_final_kernel(const double* part, int nb, long n3, float* rms,
+                                                               double* n00_sum) {
+  __shared__ double red[2][256];
+  double g = 0.0, s = 0.0;
+  for (int i = threadIdx.x; i < nb; i += 256) {
+    g += part[i];
+    s += part[nb + i];
+  }
+  red[0][threadIdx.x] = g;
+  red[1][threadIdx.x] = s;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    if ((int)threadIdx.x < w) {
+      red[0][threadIdx.x] += red[0][threadIdx.x + w];
+      red[1][threadIdx.x] += red[1][threadIdx.x + w];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) rms[0] = (float)sqrt(red[0] / (double)n3);
+  if (threadIdx.x == 0) {
+    rms[0] = (float)sqrt(red[0][0] / (double)n3);
+    n00_sum[0] = red[1][0];
+  }
 }
 
+// two threads a point, each storing half of its 32 bytes (channels 4 .. 15 are zero)
 template <typename T>
-__global__ __launch_bounds__(256) void features_kernel(const T* __restrict__ n00, const T* __restrict__ phi, int n,
+__global__ __launch_bounds__(256) void features_kernel(const T* __restrict__ n00, const T* __restrict__ phi, int lg,
                                                        const double* __restrict__ n00_sum, const float* __restrict__ rms,
                                                        uint16_t* __restrict__ out) {
-  const long n3 = (long)n * n * n;
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n3) return;
-  const int m = n - 1;
-  const int x = (int)(i % n), y = (int)((i / n) % n), z = (int)(i / ((long)n * n));
-  const long nn = (long)n * n;
-  const float hn = 0.5f * n;
-  const float mean = (float)(n00_sum[0] / (double)n3);
-  const float delta = (float)n00[i] / mean - 1.0f;
-  const float s = copysignf(log1pf(fabsf(delta)), delta);
-  const float ir = 1.0f / rms[0];
-  const float gx = (float)(phi[z * nn + y * n + ((x + 1) & m)] - phi[z * nn + y * n + ((x - 1) & m)]) * hn * ir;
-  const float gy = (float)(phi[z * nn + ((y + 1) & m) * n + x] - phi[z * nn + ((y - 1) & m) * n + x]) * hn * ir;
-  const float gz = (float)(phi[((z + 1) & m) * nn + y * n + x] - phi[((z - 1) & m) * nn + y * n + x]) * hn * ir;
-  uint4 a = make_uint4((uint32_t)f2bf(s) | ((uint32_t)f2bf(gx) << 16), (uint32_t)f2bf(gy) | ((uint32_t)f2bf(gz) << 16), 0u, 0u);
-  uint4* o = reinterpret_cast<uint4*>(out + i * 16);
-  o[0] = a;
-  o[1] = make_uint4(0u, 0u, 0u, 0u);
+  const int n = 1 << lg, m = n - 1;
+  const long q = (long)blockIdx.x * 256 + threadIdx.x, i = q >> 1;  // the grid is exact: 2 n^3 is a multiple of 256
+  uint4 a = make_uint4(0u, 0u, 0u, 0u);
+  if ((q & 1) == 0) {
+    const int x = (int)i & m, y = (int)(i >> lg) & m, z = (int)(i >> (2 * lg));
+    const long rz = (long)z << (2 * lg), ry = (long)y << lg;
+    const float hn = 0.5f * n;
+    const float mean = (float)(n00_sum[0] / (double)(1L << (3 * lg)));
+    const float delta = (float)n00[i] / mean - 1.0f;
+    const float s = copysignf(log1pf(fabsf(delta)), delta);
+    const float ir = 1.0f / rms[0];
+    const float gx = (float)(phi[rz + ry + ((x + 1) & m)] - phi[rz + ry + ((x - 1) & m)]) * hn * ir;
+    const float gy = (float)(phi[rz + ((long)((y + 1) & m) << lg) + x] - phi[rz + ((long)((y - 1) & m) << lg) + x]) * hn * ir;
+    const float gz = (float)(phi[((long)((z + 1) & m) << (2 * lg)) + ry + x] -
+                             phi[((long)((z - 1) & m) << (2 * lg)) + ry + x]) * hn * ir;
+    a.x = (uint32_t)f2bf(s) | ((uint32_t)f2bf(gx) << 16);
+    a.y = (uint32_t)f2bf(gy) | ((uint32_t)f2bf(gz) << 16);
+  }
+  reinterpret_cast<uint4*>(out)[q] = a;
 }
 
 // ---------------------------------------------------------------------------
@@ -535,7 +608,7 @@ void closure_wgrad(const uint16_t* x, const uint16_t* dy, int n, float* part, in
   const long tiles = closure_wgrad_tiles(n);
   const int grid = closure_wgrad_grid(n);
   hipLaunchKernelGGL(conv16_wgrad_kernel, dim3(grid), dim3(CV_NT), 0, st, x, dy, n, tiles, part);
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((WG_PART + 63) / 64), dim3(256), 0, st, part, grid, ci_n, co_n, grad,
+  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((WG_PART + 63) / 64), dim3(64 * WR_PARTS), 0, st, part, grid, ci_n, co_n, grad,
                      off);
 }
 
@@ -547,14 +620,17 @@ void closure_adam(float* p, float* m, float* v, const float* g, int np, double l
 }
 
 template <typename T>
-void closure_features(const T* n00, const T* phi, int n, const double* n00_sum, double* part, float* rms,
-                      uint16_t* out, hipStream_t st) {
+void closure_features(const T* n00, const T* phi, int n, double* n00_sum, double* part, float* rms, uint16_t* out,
+                      hipStream_t st) {
   const long n3 = (long)n * n * n;
-  const int nb = 512;
-  hipLaunchKernelGGL((gradsq_partial_kernel<T>), dim3(nb), dim3(256), 0, st, phi, n, part);
-  hipLaunchKernelGGL(gradsq_final_kernel, dim3(1), dim3(256), 0, st, part, nb, n3, rms);
-  hipLaunchKernelGGL((features_kernel<T>), dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0, st, n00, phi, n, n00_sum,
-                     rms, out);
+  int lg = 0;
+  while ((1 << lg) < n) ++lg;
+  const long want = (n3 / 4 + 255) / 256;
+  const int nb = (int)(want < FEAT_BLOCKS ? want : FEAT_BLOCKS);
+  hipLaunchKernelGGL((field_sums_kernel<T>), dim3(nb), dim3(256), 0, st, n00, phi, lg, part);
+  hipLaunchKernelGGL(field_sums_final_kernel, dim3(1), dim3(256), 0, st, part, nb, n3, rms, n00_sum);
+  hipLaunchKernelGGL((features_kernel<T>), dim3((unsigned)(2 * n3 / 256)), dim3(256), 0, st, n00, phi, lg, n00_sum, rms,
+                     out);
 }
 
 template <typename T>
@@ -585,7 +661,7 @@ void gather_grad_phi(const Particles<T>& p, long np, int n, const T* phi, T* out
 }
 
 #define GPM_CL_INST(T)                                                                                          \
-  template void closure_features<T>(const T*, const T*, int, const double*, double*, float*, uint16_t*, hipStream_t); \
+  template void closure_features<T>(const T*, const T*, int, double*, double*, float*, uint16_t*, hipStream_t);   \
   template void closure_gather3<T>(const Particles<T>&, long, int, const float*, float*, hipStream_t);          \
   template void closure_loss3<T>(const Particles<T>&, long, int, const float*, const float*, float*, double*,     \
                                  double*, hipStream_t);                                                          \

@@ -166,9 +166,10 @@ long closure_wgrad_part_bytes(int n);  // weight-gradient partials of one layer 
 void closure_wgrad(const uint16_t* x, const uint16_t* dy, int n, float* part, int ci_n, int co_n, float* grad,
                    long off, hipStream_t st);
 void closure_adam(float* p, float* m, float* v, const float* g, int np, double lr, int step, hipStream_t st);
+// the network's input from n00 and phi; writes the FP64 sum of n00 and rms |grad phi| too; part: 4096 doubles of scratch
 template <typename T>
-void closure_features(const T* n00, const T* phi, int n, const double* n00_sum, double* part, float* rms,
-                      uint16_t* out, hipStream_t st);
+void closure_features(const T* n00, const T* phi, int n, double* n00_sum, double* part, float* rms, uint16_t* out,
+                      hipStream_t st);
 template <typename T>
 void closure_gather3(const Particles<T>& p, long np, int n, const float* f, float* out, hipStream_t st);
 // pred - target at the particles: dpred = 2 (pred - target) / (3 np), out[0] = mean |pred - target|^2,

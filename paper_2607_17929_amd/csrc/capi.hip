@@ -261,18 +261,23 @@ struct pm_ctx {
     ev_n[s] += 1;
   }
 
-  template <typename T> Particles<T> parts_at(size_t pos, size_t mom, size_t ids, long cnt) {
+  // A particle buffer (the three regions at pos, mom and ids lie one after the other) holds the records of the store,
+  // a skew apart; or, as scratch, separate arrays: [n][3] inputs and outputs, or those of a checkpoint.
+  template <typename T> Particles<T> parts_at(size_t pos, long cnt) {
+    auto next = [&](size_t o, size_t bytes) { return align_up(o + bytes) + kSkew; };
     Particles<T> p;
-    double* pb = at<double>(pos);
-    T* mb = at<T>(mom);
-    const long sd = (long)(kSkew / sizeof(double)), st_ = (long)(kSkew / sizeof(T));
-    p.px = pb; p.py = pb + cnt + sd; p.pz = pb + 2 * (cnt + sd);
-    p.ux = mb; p.uy = mb + cnt + st_; p.uz = mb + 2 * (cnt + st_);
-    p.id = at<uint32_t>(ids);
+    size_t o = pos;
+    p.a = at<PartA>(o);
+    o = next(o, cnt * sizeof(PartA));
+    p.b = at<PartB<T>>(o);
+    o = next(o, cnt * sizeof(PartB<T>));
+    p.c = at<PartC<T>>(o);
+    o = next(o, cnt * sizeof(PartC<T>));
+    p.id = at<uint32_t>(o);
     return p;
   }
-  template <typename T> Particles<T> parts(int b) { return parts_at<T>(L.pos[b], L.mom[b], L.ids[b], np); }
-  template <typename T> Particles<T> parts2(int b) { return parts_at<T>(L.pos2[b], L.mom2[b], L.ids2[b], np2); }
+  template <typename T> Particles<T> parts(int b) { return parts_at<T>(L.pos[b], np); }
+  template <typename T> Particles<T> parts2(int b) { return parts_at<T>(L.pos2[b], np2); }
   void* field_ptr(int id) {
     if (id >= PM_FIELD_N00 && id <= PM_FIELD_NZZ) {
       if (id >= L.ndep) return nullptr;
@@ -838,7 +843,7 @@ pm_status pm_diagnostics(pm_ctx* c, double* out, int n) {
   if (!c->have_particles || (c->np2 > 0 && !c->have_particles2)) return c->fail(PM_ESTATE, "no particles");
   if (c->sticky) return (pm_status)c->sticky;
   double* sc = c->at<double>(c->L.scal);
-  // total momentum per unit mass of species 1: FP64 sums of the SoA momenta (scalars 3..5 for species 1,
+  // total momentum per unit mass of species 1: FP64 sums of the momenta (scalars 3..5 for species 1,
   // then 3..5 again for species 2 after species 1's were read)
   double mom[3] = {0, 0, 0};
   for (int s = 0; s < (c->np2 > 0 ? 2 : 1); ++s) {
@@ -846,12 +851,12 @@ pm_status pm_diagnostics(pm_ctx* c, double* out, int n) {
     for (int d = 0; d < 3; ++d) {
       if (c->cfg.precision == PM_FP64) {
         const Particles<double> p = s == 0 ? c->parts<double>(c->cur) : c->parts2<double>(c->cur2);
-        const double* u = d == 0 ? p.ux : (d == 1 ? p.uy : p.uz);
-        launch_sum_f64(u, s == 0 ? c->np : c->np2, sc + 3 + d, c->st);
+        const double* u = d == 0 ? &p.b->ux : (d == 1 ? &p.c->uy : &p.c->uz);
+        launch_sum_f64(u, s == 0 ? c->np : c->np2, sc + 3 + d, c->st, 2);
       } else {
         const Particles<float> p = s == 0 ? c->parts<float>(c->cur) : c->parts2<float>(c->cur2);
-        const float* u = d == 0 ? p.ux : (d == 1 ? p.uy : p.uz);
-        launch_sum_as_f64(u, s == 0 ? c->np : c->np2, sc + 3 + d, c->st);
+        const float* u = d == 0 ? &p.b->ux : (d == 1 ? &p.b->uy : &p.c->uz);
+        launch_sum_as_f64(u, s == 0 ? c->np : c->np2, sc + 3 + d, c->st, d < 2 ? 4 : 1);
       }
     }
     double h[6];
@@ -1026,10 +1031,10 @@ struct StateHeader {
 };
 static_assert(sizeof(StateHeader) <= kStateHeader, "state header too large");
 
-// workspace regions that make up the state: the sorted particles (buffer `cur`), the cell offsets
-// of the sort, phi of the latest and the previous solve and the latest solve's increment, chi, B,
-// the tensor and parabolic-B spectra, the FP64 scalars and, between a deposit and its solve, the
-// deposit
+// workspace regions that make up the state: the sorted particles (as separate arrays in buffer `cur`, which is not the
+// one that holds the store), the cell offsets of the sort, phi of the latest and the previous solve and the latest
+// solve's increment, chi, B, the tensor and parabolic-B spectra, the FP64 scalars and, between a deposit and its
+// solve, the deposit
 int state_sections(const pm_ctx* c, int cur, int cur2, int i_phi, int i_prev, bool with_dep, size_t* ws_off,
                    size_t* bytes) {
   const Layout& L = c->L;
@@ -1061,6 +1066,25 @@ int state_sections(const pm_ctx* c, int cur, int cur2, int i_phi, int i_prev, bo
   return k;
 }
 
+// the store of buffer `from` as separate arrays in buffer `to`, and back
+template <typename T>
+void state_arrays(pm_ctx* c, int from, int from2, int to, int to2, bool unpack) {
+  const Layout& L = c->L;
+  if (unpack) {
+    launch_unpack<T>(c->parts<T>(from), c->np, c->at<double>(L.pos[to]), c->at<T>(L.mom[to]),
+                     c->at<uint32_t>(L.ids[to]), (long)kSkew, c->st);
+    if (c->np2 > 0)
+      launch_unpack<T>(c->parts2<T>(from2), c->np2, c->at<double>(L.pos2[to2]), c->at<T>(L.mom2[to2]),
+                       c->at<uint32_t>(L.ids2[to2]), (long)kSkew, c->st);
+  } else {
+    launch_pack<T>(c->at<double>(L.pos[from]), c->at<T>(L.mom[from]), c->at<uint32_t>(L.ids[from]), c->np, (long)kSkew,
+                   c->parts<T>(to), c->st);
+    if (c->np2 > 0)
+      launch_pack<T>(c->at<double>(L.pos2[from2]), c->at<T>(L.mom2[from2]), c->at<uint32_t>(L.ids2[from2]), c->np2,
+                     (long)kSkew, c->parts2<T>(to2), c->st);
+  }
+}
+
 size_t state_blob_offsets(int nsec, const size_t* bytes, uint64_t* off) {
   size_t o = kStateHeader;
   for (int i = 0; i < nsec; ++i) {
@@ -1080,7 +1104,7 @@ pm_status pm_get_state(pm_ctx* c, void* blob, size_t* bytes, int dst_on_device) 
   if (c->np2 > 0 && !c->have_particles2) return c->fail(PM_ESTATE, "no second species loaded");
   if (c->sticky) return (pm_status)c->sticky;
   size_t ws_off[kStateMaxSec], sb[kStateMaxSec];
-  const int nsec = state_sections(c, c->cur, c->cur2, c->i_phi, c->i_prev, c->deposited, ws_off, sb);
+  const int nsec = state_sections(c, 1 - c->cur, 1 - c->cur2, c->i_phi, c->i_prev, c->deposited, ws_off, sb);
   StateHeader h;
   memset(&h, 0, sizeof(h));
   const size_t total = state_blob_offsets(nsec, sb, h.off);
@@ -1113,6 +1137,8 @@ pm_status pm_get_state(pm_ctx* c, void* blob, size_t* bytes, int dst_on_device) 
   for (int i = 0; i < nsec; ++i) h.bytes[i] = sb[i];
   unsigned char* dst = reinterpret_cast<unsigned char*>(blob);
   const hipMemcpyKind kind = dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+  if (c->cfg.precision == PM_FP64) state_arrays<double>(c, c->cur, c->cur2, 1 - c->cur, 1 - c->cur2, true);
+  else state_arrays<float>(c, c->cur, c->cur2, 1 - c->cur, 1 - c->cur2, true);
   // the whole header block, zero beyond the struct
   std::vector<unsigned char> head(kStateHeader, 0);
   memcpy(head.data(), &h, sizeof(h));
@@ -1155,10 +1181,10 @@ pm_status pm_set_state(pm_ctx* c, const void* blob, size_t bytes, int src_on_dev
     return c->fail(PM_EINVAL, "state blob of another configuration");
   if (!(h.tau > 0) || !isfinite(h.tau) || h.steps < 0 || h.total > bytes)
     return c->fail(PM_EINVAL, "corrupt state header");
-  // restore into particle buffer 0 and phi slots 0 (latest), 1 (previous) and 2 (increment)
+  // restore into particle buffer 0 (by way of buffer 1) and phi slots 0 (latest), 1 (previous) and 2 (increment)
   size_t ws_off[kStateMaxSec], sb[kStateMaxSec];
   uint64_t off[kStateMaxSec];
-  const int nsec = state_sections(c, 0, 0, 0, 1, h.deposited != 0, ws_off, sb);
+  const int nsec = state_sections(c, 1, 1, 0, 1, h.deposited != 0, ws_off, sb);
   const size_t total = state_blob_offsets(nsec, sb, off);
   if ((int)h.nsec != nsec || h.total != total) return c->fail(PM_EINVAL, "corrupt state header");
   for (int i = 0; i < nsec; ++i)
@@ -1166,6 +1192,8 @@ pm_status pm_set_state(pm_ctx* c, const void* blob, size_t bytes, int src_on_dev
   const unsigned char* src = reinterpret_cast<const unsigned char*>(blob);
   const hipMemcpyKind kind = src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
   for (int i = 0; i < nsec; ++i) (void)hipMemcpyAsync(c->ws + ws_off[i], src + off[i], sb[i], kind, c->st);
+  if (c->cfg.precision == PM_FP64) state_arrays<double>(c, 1, 1, 0, 0, false);
+  else state_arrays<float>(c, 1, 1, 0, 0, false);
   // the per-cell counters are zero between sorts; the device error flag starts clear
   c->zero(c->L.cnt, c->n3 * 4);
   if (c->np2 > 0) c->zero(c->L.cnt2, c->n3 * 4);
@@ -1327,11 +1355,10 @@ pm_status pm_closure_backward(pm_ctx* c, const float* d_dpred, float* d_grad) {
   const uint16_t* a2 = c->at<uint16_t>(L.cl_act[2]);
   const uint16_t* wb = c->at<uint16_t>(L.cl_wb);
   float* part = c->at<float>(L.cl_part);
-  auto adjoint = [&](const auto& p) {
-    launch_deposit_vectors(p.px, p.py, p.pz, p.id, c->at<uint32_t>(L.cell_start), n, d_dpred, d3, c->st);
-  };
-  if (c->cfg.precision == PM_FP64) adjoint(c->parts<double>(c->cur));
-  else adjoint(c->parts<float>(c->cur));
+  if (c->cfg.precision == PM_FP64)
+    launch_deposit_vectors<double>(c->parts<double>(c->cur), c->at<uint32_t>(L.cell_start), n, d_dpred, d3, c->st);
+  else
+    launch_deposit_vectors<float>(c->parts<float>(c->cur), c->at<uint32_t>(L.cell_start), n, d_dpred, d3, c->st);
   const long off2 = 16 * 4 * 27 + 16, off3 = off2 + 16 * 16 * 27 + 16;
   closure_wgrad(a2, d3, n, part, 16, 3, d_grad, off3, c->st);
   closure_conv(d3, wb + 2 * 27 * 256, nullptr, n, 2, d2, a2, nullptr, c->st);

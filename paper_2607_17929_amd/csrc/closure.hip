@@ -423,9 +423,11 @@ __device__ __forceinline__ void gather3_at(const Particles<T>& p, long i, int n,
                                            float v[3]) {
   int x0, x1, y0, y1, z0, z1;
   float wx0, wx1, wy0, wy1, wz0, wz1;
-  cic(p.px[i], n, x0, x1, wx0, wx1);
-  cic(p.py[i], n, y0, y1, wy0, wy1);
-  cic(p.pz[i], n, z0, z1, wz0, wz1);
+  Particle<T> q;
+  load_pos(p, i, q);
+  cic(q.x, n, x0, x1, wx0, wx1);
+  cic(q.y, n, y0, y1, wy0, wy1);
+  cic(q.z, n, z0, z1, wz0, wz1);
   const long nn = (long)n * n, n3 = nn * n;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -444,8 +446,7 @@ __global__ __launch_bounds__(256) void gather3_kernel(Particles<T> p, long np, i
   if (i >= np) return;
   float v[3];
   gather3_at(p, i, n, f, v);
-  const long id = p.id[i];
-  for (int c = 0; c < 3; ++c) out[3 * id + c] = v[c];
+  *reinterpret_cast<V3<float>*>(out + 3 * (long)load_id(p, i)) = V3<float>{v[0], v[1], v[2]};
 }
 
 // Training residual: pred = gathered network output, r = pred - target (FP32, identifier order),
@@ -460,15 +461,18 @@ __global__ __launch_bounds__(256) void loss3_kernel(Particles<T> p, long np, int
   for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < np; i += (long)gridDim.x * 256) {
     float v[3];
     gather3_at(p, i, n, f, v);
-    const long id = p.id[i];
+    const long id = load_id(p, i);
+    const V3<float> t3 = *reinterpret_cast<const V3<float>*>(target + 3 * id);
+    const float tg[3] = {t3.x, t3.y, t3.z};
+    float d[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const float tg = target[3 * id + c];
-      const float r = v[c] - tg;
-      dpred[3 * id + c] = r * gscale;
+      const float r = v[c] - tg[c];
+      d[c] = r * gscale;
       e2 += (double)r * (double)r;
-      t2 += (double)tg * (double)tg;
+      t2 += (double)tg[c] * (double)tg[c];
     }
+    *reinterpret_cast<V3<float>*>(dpred + 3 * id) = V3<float>{d[0], d[1], d[2]};
   }
   red[0][threadIdx.x] = e2;
   red[1][threadIdx.x] = t2;
@@ -554,7 +558,9 @@ __global__ __launch_bounds__(256) void gather_grad_phi_kernel(Particles<T> p, lo
   int ix[2], iy[2], iz[2];
   T wx[2], wy[2], wz[2];
   {
-    const double sx = p.px[i] * (double)n, sy = p.py[i] * (double)n, sz = p.pz[i] * (double)n;
+    Particle<T> q;
+    load_pos(p, i, q);
+    const double sx = q.x * (double)n, sy = q.y * (double)n, sz = q.z * (double)n;
     const double fx = floor(sx), fy = floor(sy), fz = floor(sz);
     ix[0] = ((int)fx) & m; iy[0] = ((int)fy) & m; iz[0] = ((int)fz) & m;
     ix[1] = (ix[0] + 1) & m; iy[1] = (iy[0] + 1) & m; iz[1] = (iz[0] + 1) & m;
@@ -571,9 +577,8 @@ __global__ __launch_bounds__(256) void gather_grad_phi_kernel(Particles<T> p, lo
         g[1] += w * (phi[z * nn + ((y + 1) & m) * n + x] - phi[z * nn + ((y - 1) & m) * n + x]);
         g[2] += w * (phi[((z + 1) & m) * nn + y * n + x] - phi[((z - 1) & m) * nn + y * n + x]);
       }
-  const long id = p.id[i];
   const T hn = (T)(0.5 * n);
-  for (int d = 0; d < 3; ++d) out[3 * id + d] = g[d] * hn;
+  *reinterpret_cast<V3<T>*>(out + 3 * (long)load_id(p, i)) = V3<T>{g[0] * hn, g[1] * hn, g[2] * hn};
 }
 
 // ---------------------------------------------------------------------------

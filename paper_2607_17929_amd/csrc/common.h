@@ -93,6 +93,9 @@ __device__ __forceinline__ int wrapi(int i, int n) { return i & (n - 1); }
 // four values read or written as one aligned LDS access
 template <typename T> struct alignas(4 * sizeof(T)) V4 { T x, y, z, w; };
 
+// three values next to each other in memory (aligned as one value): one or two wide accesses
+template <typename T> struct V3 { T x, y, z; };
+
 // Reciprocal and reciprocal square root: the FP32 path uses the hardware
 // instructions (about 1 ulp), the FP64 path the correctly rounded operations.
 template <typename T> __device__ __forceinline__ T rcp(T x) { return (T)1 / x; }

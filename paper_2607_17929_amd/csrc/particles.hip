@@ -1,10 +1,11 @@
 // Particle kernels: ingest, CIC deposit, gather + kick + drift, counting sort by cell.
 //
-// The particle store is a structure of arrays (x, y, z in FP64; u_x, u_y, u_z
-// and the identifier) kept sorted by mesh cell in row-major order
+// The particle store (arrays of records, kernels.h) is kept sorted by mesh cell in row-major order
 // key = (iz n + iy) n + ix, so that the particles of one x-row of cells are
 // contiguous and ordered along x, as in the paper's particle handler
 // (Sec. 2.1).  cell_start[key] .. cell_start[key + 1] is the range of a cell.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace gpm {
@@ -32,7 +33,7 @@ __device__ __forceinline__ uint32_t cell_key(double x, double y, double z, int n
 }
 
 // ---------------------------------------------------------------------------
-// ingest: [n][3] inputs -> SoA, wrap, validate, rank within the cell
+// ingest: [n][3] inputs -> store, wrap, validate, rank within the cell
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void ingest_kernel(const double* pos, const T* u, const uint32_t* ids, long np,
@@ -40,8 +41,10 @@ __global__ __launch_bounds__(256) void ingest_kernel(const double* pos, const T*
                                                      int* err) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= np) return;
-  double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
-  T ux = u[3 * i], uy = u[3 * i + 1], uz = u[3 * i + 2];
+  const V3<double> pi = *reinterpret_cast<const V3<double>*>(pos + 3 * i);
+  const V3<T> ui = *reinterpret_cast<const V3<T>*>(u + 3 * i);
+  double x = pi.x, y = pi.y, z = pi.z;
+  T ux = ui.x, uy = ui.y, uz = ui.z;
   if (!(isfinite(x) && isfinite(y) && isfinite(z) && isfinite(ux) && isfinite(uy) && isfinite(uz))) {
     atomicOr(err, 1);
     x = y = z = 0.0;
@@ -53,9 +56,7 @@ __global__ __launch_bounds__(256) void ingest_kernel(const double* pos, const T*
     atomicOr(err, 2);
     id = 0;
   }
-  out.px[i] = x; out.py[i] = y; out.pz[i] = z;
-  out.ux[i] = ux; out.uy[i] = uy; out.uz[i] = uz;
-  out.id[i] = id;
+  store_particle(out, i, Particle<T>{x, y, z, ux, uy, uz, id});
   const uint32_t k = cell_key(x, y, z, nmesh);
   rank[i] = atomicAdd(&cnt[k], 1u);
 }
@@ -125,13 +126,6 @@ __device__ __forceinline__ int row_of(const uint32_t* off, uint32_t i) {
 }
 
 typedef double v4d __attribute__((ext_vector_type(4)));
-
-// One particle in registers (loaded for the next plane while the current one is summed).
-template <typename T>
-struct DepPart {
-  double x, y, z;
-  T ux, uy, uz;
-};
 
 template <typename T, int NC, bool REL, int TX, int DEP_NT>
 __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel(Particles<T> p, const uint32_t* __restrict__ cell_start, int n,
@@ -210,17 +204,23 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
     own = r > 0 && k >= hn;
     return k < hn ? hs + k : raw[b][r][2] + (k - hn);
   };
-  auto load_part = [&](uint32_t g, DepPart<T>& d) {
-    d.x = p.px[g]; d.y = p.py[g]; d.z = p.pz[g];
+  using Held = std::conditional_t<(NC > 4), Loaded<T>, Particle<T>>;
+  auto load_part = [&](uint32_t g, Held& d) {
+    if constexpr (NC > 4) {
+      load_raw_state(p, g, d);
+    } else {
+      load_pos(p, g, d);
+    }
     if constexpr (VEC) {
-      const long id = p.id[g];
+      const long id = load_id(p, g);
       d.ux = vals[3 * id]; d.uy = vals[3 * id + 1]; d.uz = vals[3 * id + 2];
-    } else if constexpr (NC > 1) {
-      d.ux = p.ux[g]; d.uy = p.uy[g]; d.uz = p.uz[g];
     }
   };
   double e_own = 0.0;
-  auto stage = [&](uint32_t l, const DepPart<T>& d, bool own) {
+  auto stage = [&](uint32_t l, const Held& held, bool own) {
+    Particle<T> d;
+    if constexpr (NC > 4) d = unpacked(held);
+    else d = held;
     const double sx = d.x * (double)n, sy = d.y * (double)n, sz = d.z * (double)n;
     V4<T> fr;
     fr.x = (T)(sx - floor(sx));
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
   scan_rows(0);
   scan_rows(1);
   __syncthreads();
-  DepPart<T> pr[SPT];
+  Held pr[SPT];
   bool pown[SPT];
   {
     const uint32_t lim = min(roff[0][ROWS], (uint32_t)CAP);
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
         const uint32_t i = c0 + here() + s2 * DEP_NT;
         if (i < c1) {
           bool own;
-          DepPart<T> d;
+          Held d;
           load_part(source_of(b, i, own), d);
           stage(i - c0, d, own && P > 0);
         }
@@ -551,13 +551,11 @@ void launch_deposit(const Particles<T>& p, const uint32_t* cell_start, int n, in
 }
 
 // Adjoint of the CIC gather of three fields: the sums over particles of W vals[id] as bfloat16
-// [vertex][16], channels 3 .. 15 zero.  The store's momenta are not read, so one FP32 instance serves both
-// precisions.  (By FP32 atomics into three fields and a conversion pass: 1.85 ms at 128^3 with crowded cells.)
-void launch_deposit_vectors(const double* px, const double* py, const double* pz, const uint32_t* id,
-                            const uint32_t* cell_start, int n, const float* vals, uint16_t* out, hipStream_t st) {
-  Particles<float> p = {const_cast<double*>(px), const_cast<double*>(py), const_cast<double*>(pz), nullptr, nullptr,
-                        nullptr, const_cast<uint32_t*>(id)};
-  launch_deposit_nc<float, 3, false>(p, cell_start, n, 0.0, 1.0, false, reinterpret_cast<float*>(out), nullptr, vals, st);
+// [vertex][16], channels 3 .. 15 zero.  (By FP32 atomics into three fields and a conversion pass: 1.85 ms at 128^3 with crowded cells.)
+template <typename T>
+void launch_deposit_vectors(const Particles<T>& p, const uint32_t* cell_start, int n, const float* vals, uint16_t* out,
+                            hipStream_t st) {
+  launch_deposit_nc<T, 3, false>(p, cell_start, n, 0.0, 1.0, false, reinterpret_cast<T*>(out), nullptr, vals, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -695,25 +693,19 @@ __global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T>
   // each thread takes particles tid, tid + KD_NT, ...; the next one's state is read while the
   // current one is processed
   uint32_t pin = 0;
-  double xn = 0.0, yn = 0.0, zn = 0.0;
-  T uxn = 0, uyn = 0, uzn = 0;
-  if ((uint32_t)tid < total) {
-    const int r = row_of<NR>(roff, tid);
-    pin = rbeg[r] + (tid - roff[r]);
-    xn = p.px[pin]; yn = p.py[pin]; zn = p.pz[pin];
-    uxn = p.ux[pin]; uyn = p.uy[pin]; uzn = p.uz[pin];
-  }
+  Loaded<T> next = {};
+  auto load_next = [&](uint32_t i) {
+    const int r = row_of<NR>(roff, i);
+    pin = rbeg[r] + (i - roff[r]);
+    load_raw_state(p, pin, next);
+  };
+  if ((uint32_t)tid < total) load_next(tid);
   for (uint32_t i = tid; i < total; i += KD_NT) {
     const uint32_t pi = pin;
-    double x = xn, y = yn, z = zn;
-    T ux = uxn, uy = uyn, uz = uzn;
-    const uint32_t inx = i + KD_NT;
-    if (inx < total) {
-      const int r = row_of<NR>(roff, inx);
-      pin = rbeg[r] + (inx - roff[r]);
-      xn = p.px[pin]; yn = p.py[pin]; zn = p.pz[pin];
-      uxn = p.ux[pin]; uyn = p.uy[pin]; uzn = p.uz[pin];
-    }
+    const Particle<T> now = unpacked(next);
+    double x = now.x, y = now.y, z = now.z;
+    T ux = now.ux, uy = now.uy, uz = now.uz;
+    if (i + KD_NT < total) load_next(i + KD_NT);
     int ix, iy, iz;
     double fxd, fyd, fzd;
     cell_of(x, n, ix, fxd);
@@ -787,8 +779,7 @@ __global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T>
       x = y = z = 0.0;
     }
     x = wrap01(x); y = wrap01(y); z = wrap01(z);
-    p.px[pi] = x; p.py[pi] = y; p.pz[pi] = z;
-    p.ux[pi] = ux; p.uy[pi] = uy; p.uz[pi] = uz;
+    store_state(p, pi, Particle<T>{x, y, z, ux, uy, uz, 0u});
     rank[pi] = rank_in_cell(cnt, cell_key(x, y, z, n));
   }
 }
@@ -971,10 +962,11 @@ void launch_scan(uint32_t* cnt, uint32_t* cell_start, long ncell, uint32_t* bloc
 
 // ---------------------------------------------------------------------------
 // scatter into the other buffer at cell_start[cell] + rank; the cell is
-// recomputed from the stored position exactly as the kick/drift computed it
+// recomputed from the stored position exactly as the kick/drift computed it.
+// Bound by the scattered stores, 16 + 16 + 4 + 4 bytes apart by particles that left their neighbours
+// (512^3 FP32: 3.0 TB/s of 84 bytes each; a stream of the same bytes takes 2.6 ms of the sort's 3.9).
+// One particle per thread: two or four in flight gain nothing (3.92, 4.07 and 4.11 ms).
 // ---------------------------------------------------------------------------
-constexpr int SC_PER = 2;  // particles per thread: independent load chains in flight (2 measured best of 2, 4, 8)
-
 template <typename T>
 __global__ __launch_bounds__(256) void scatter_kernel(Particles<T> s, Particles<T> d, long np, int nmesh,
                                                       const uint32_t* __restrict__ rank,
@@ -982,41 +974,20 @@ __global__ __launch_bounds__(256) void scatter_kernel(Particles<T> s, Particles<
                                                       int nreset) {
   // counts left standing by the scan
   for (int c = (int)(blockIdx.x * 256 + threadIdx.x); c < nreset; c += (int)(gridDim.x * 256)) cnt[c] = 0u;
-  const long base = (long)xcd_remap(blockIdx.x, gridDim.x) * (256 * SC_PER) + threadIdx.x;
-  // every read that does not depend on the destination is issued first
-  uint32_t r[SC_PER], id[SC_PER];
-  double x[SC_PER], y[SC_PER], z[SC_PER];
-  T ux[SC_PER], uy[SC_PER], uz[SC_PER];
-#pragma unroll
-  for (int q = 0; q < SC_PER; ++q) {
-    const long i = base + q * 256;
-    if (i < np) {
-      r[q] = rank[i];
-      x[q] = s.px[i]; y[q] = s.py[i]; z[q] = s.pz[i];
-      ux[q] = s.ux[i]; uy[q] = s.uy[i]; uz[q] = s.uz[i];
-      id[q] = s.id[i];
-    }
-  }
-  long j[SC_PER];
-#pragma unroll
-  for (int q = 0; q < SC_PER; ++q)
-    j[q] = (base + q * 256 < np) ? (long)cell_start[cell_key(x[q], y[q], z[q], nmesh)] + r[q] : 0;
-#pragma unroll
-  for (int q = 0; q < SC_PER; ++q) {
-    if (base + q * 256 < np) {
-      d.px[j[q]] = x[q]; d.py[j[q]] = y[q]; d.pz[j[q]] = z[q];
-      d.ux[j[q]] = ux[q]; d.uy[j[q]] = uy[q]; d.uz[j[q]] = uz[q];
-      d.id[j[q]] = id[q];
-    }
-  }
+  const long i = (long)xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  if (i >= np) return;
+  const uint32_t r = rank[i];
+  Particle<T> v;
+  load_particle(s, i, v);
+  store_particle(d, (long)cell_start[cell_key(v.x, v.y, v.z, nmesh)] + r, v);
 }
 
 template <typename T>
 void launch_scatter(const Particles<T>& src, Particles<T> dst, long np, int nmesh, const uint32_t* rank,
                     const uint32_t* cell_start, uint32_t* cnt, hipStream_t st) {
-  const long per_block = 256 * SC_PER, ncell = (long)nmesh * nmesh * nmesh;
+  const long ncell = (long)nmesh * nmesh * nmesh;
   const int nreset = scan_from_counts(ncell) ? (int)ncell : 0;
-  hipLaunchKernelGGL((scatter_kernel<T>), dim3((unsigned)((np + per_block - 1) / per_block)), dim3(256), 0, st, src, dst,
+  hipLaunchKernelGGL((scatter_kernel<T>), dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, src, dst,
                      np, nmesh, rank, cell_start, cnt, nreset);
 }
 
@@ -1032,17 +1003,13 @@ __global__ __launch_bounds__(256) void order_by_id_kernel(Particles<T> s, Partic
                                                           const uint32_t* __restrict__ cell_start) {
   const long i = (long)xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (i >= np) return;
-  const double x = s.px[i], y = s.py[i], z = s.pz[i];
-  const T ux = s.ux[i], uy = s.uy[i], uz = s.uz[i];
-  const uint32_t id = s.id[i];
-  const uint32_t k = cell_key(x, y, z, nmesh);
+  Particle<T> v;
+  load_particle(s, i, v);
+  const uint32_t k = cell_key(v.x, v.y, v.z, nmesh);
   const uint32_t b = cell_start[k], e = cell_start[k + 1];
   uint32_t r = 0;
-  for (uint32_t j = b; j < e; ++j) r += s.id[j] < id ? 1u : 0u;
-  const long o = (long)b + r;
-  d.px[o] = x; d.py[o] = y; d.pz[o] = z;
-  d.ux[o] = ux; d.uy[o] = uy; d.uz[o] = uz;
-  d.id[o] = id;
+  for (uint32_t j = b; j < e; ++j) r += load_id(s, j) < v.id ? 1u : 0u;
+  store_particle(d, (long)b + r, v);
 }
 
 template <typename T>
@@ -1073,11 +1040,12 @@ __global__ __launch_bounds__(256) void check_store_kernel(Particles<T> p, long n
                                                           const uint32_t* cell_start, int* err) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= np) return;
-  const double x = p.px[i], y = p.py[i], z = p.pz[i];
-  const T ux = p.ux[i], uy = p.uy[i], uz = p.uz[i];
-  bool ok = isfinite(ux) && isfinite(uy) && isfinite(uz);
+  Particle<T> v;
+  load_particle(p, i, v);
+  const double x = v.x, y = v.y, z = v.z;
+  bool ok = isfinite(v.ux) && isfinite(v.uy) && isfinite(v.uz);
   ok = ok && x >= 0.0 && x < 1.0 && y >= 0.0 && y < 1.0 && z >= 0.0 && z < 1.0;  // false for NaN
-  ok = ok && (long)p.id[i] < np;
+  ok = ok && (long)v.id < np;
   if (ok) {
     const uint32_t k = cell_key(x, y, z, nmesh);
     ok = (long)cell_start[k] <= i && i < (long)cell_start[k + 1];
@@ -1096,15 +1064,57 @@ void launch_check_store(const Particles<T>& p, long np, int nmesh, const uint32_
 }
 
 // ---------------------------------------------------------------------------
+// the store as separate arrays and back (checkpoints)
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(256) void unpack_kernel(Particles<T> p, long n, double* pos, T* mom, uint32_t* ids, long gap) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  const long sp = n + gap / (long)sizeof(double), sm = n + gap / (long)sizeof(T);
+  if (i < gap / (long)sizeof(T)) {
+    mom[n + i] = mom[sm + n + i] = (T)0;
+    if (i < gap / (long)sizeof(double)) pos[n + i] = pos[sp + n + i] = 0.0;
+  }
+  if (i >= n) return;
+  Particle<T> v;
+  load_particle(p, i, v);
+  pos[i] = v.x; pos[sp + i] = v.y; pos[2 * sp + i] = v.z;
+  mom[i] = v.ux; mom[sm + i] = v.uy; mom[2 * sm + i] = v.uz;
+  ids[i] = v.id;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void pack_kernel(const double* pos, const T* mom, const uint32_t* ids, long n, long gap,
+                                                   Particles<T> p) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const long sp = n + gap / (long)sizeof(double), sm = n + gap / (long)sizeof(T);
+  store_particle(p, i, Particle<T>{pos[i], pos[sp + i], pos[2 * sp + i], mom[i], mom[sm + i], mom[2 * sm + i], ids[i]});
+}
+
+template <typename T>
+void launch_unpack(const Particles<T>& p, long n, double* pos, T* mom, uint32_t* ids, long gap, hipStream_t st) {
+  const long m = n > gap ? n : gap;
+  hipLaunchKernelGGL((unpack_kernel<T>), dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, p, n, pos, mom, ids, gap);
+}
+
+template <typename T>
+void launch_pack(const double* pos, const T* mom, const uint32_t* ids, long n, long gap, const Particles<T>& p,
+                 hipStream_t st) {
+  hipLaunchKernelGGL((pack_kernel<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos, mom, ids, n, gap, p);
+}
+
+// ---------------------------------------------------------------------------
 // export in identifier order as [n][3] arrays
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void export_kernel(Particles<T> p, long np, double* pos, T* u, uint32_t* ids) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= np) return;
-  const long d = p.id[i];
-  if (pos) { pos[3 * d] = p.px[i]; pos[3 * d + 1] = p.py[i]; pos[3 * d + 2] = p.pz[i]; }
-  if (u) { u[3 * d] = p.ux[i]; u[3 * d + 1] = p.uy[i]; u[3 * d + 2] = p.uz[i]; }
+  Particle<T> v;
+  load_particle(p, i, v);
+  const long d = v.id;
+  if (pos) *reinterpret_cast<V3<double>*>(pos + 3 * d) = V3<double>{v.x, v.y, v.z};
+  if (u) *reinterpret_cast<V3<T>*>(u + 3 * d) = V3<T>{v.ux, v.uy, v.uz};
   if (ids) ids[d] = (uint32_t)d;
 }
 
@@ -1147,6 +1157,10 @@ void launch_copy_unpad(const cplx<T>* spec, int n, int nhp, cplx<T>* out, bool t
                                      uint32_t*, int*, hipStream_t);                                                    \
   template void launch_scatter<T>(const Particles<T>&, Particles<T>, long, int, const uint32_t*, const uint32_t*,      \
                                   uint32_t*, hipStream_t);                                                                        \
+  template void launch_unpack<T>(const Particles<T>&, long, double*, T*, uint32_t*, long, hipStream_t);               \
+  template void launch_pack<T>(const double*, const T*, const uint32_t*, long, long, const Particles<T>&, hipStream_t); \
+  template void launch_deposit_vectors<T>(const Particles<T>&, const uint32_t*, int, const float*, uint16_t*,         \
+                                          hipStream_t);                                                               \
   template void launch_export<T>(const Particles<T>&, long, double*, T*, uint32_t*, hipStream_t);                      \
   template void launch_check_store<T>(const Particles<T>&, long, int, const uint32_t*, int*, hipStream_t);            \
   template void launch_order_by_id<T>(const Particles<T>&, Particles<T>, long, int, const uint32_t*, hipStream_t);     \

@@ -317,3 +317,43 @@ def test_deterministic_runs_and_restart_are_bitwise_equal(precision, physics, b_
     for name in ref[0]:
         assert rel_l2(plain[0][name], ref[0][name]) < tol, name
     assert periodic_max_dx(plain[1], ref[1], n) < (1e-9 if precision == "fp64" else 1e-4)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_blob_holds_the_particles_as_separate_arrays(precision):
+    """The sections of the particles are x | y | z, u_x | u_y | u_z (1280 bytes after each of the first two arrays)
+    and the identifiers, in the order of the cells, whatever records the store itself keeps; the same bytes are
+    restored.  Odd counts, so that no array ends on a vector boundary; exact (bytes are moved, not computed)."""
+    from paper_2607_17929_amd import PMContext
+    _say(f"blob layout {precision}")
+    n, n1, n2, gap = 16, 1001, 333, 1280
+    rng = np.random.default_rng(5)
+    ctx = PMContext(n, n1, 100.0, physics="newtonian", precision=precision, n_particles_2=n2, mass_fraction_2=0.25)
+    sets = []
+    for m in (n1, n2):
+        sets.append((rng.random((m, 3)), (1e-3 * rng.standard_normal((m, 3))).astype(ctx.np_dtype)))
+    ctx.init_particles(*sets[0], 0.1)
+    ctx.init_particles_2(*sets[1])
+    ctx.step(1e-3)
+    blob = ctx.get_state()
+    head = blob[:1024].view(np.uint64)
+    off = head[14:46].astype(np.int64)  # after 112 bytes of scalars
+    rs = np.dtype(ctx.np_dtype).itemsize
+    for k, (m, get) in enumerate(((n1, ctx.get_particles), (n2, ctx.get_particles_2))):
+        o_pos, o_mom, o_id = off[4 * k:4 * k + 3]
+        ids = blob[o_id:o_id + 4 * m].view(np.uint32)
+        assert np.array_equal(np.sort(ids), np.arange(m))
+        pos, u = get()
+        cell = np.floor(pos[ids] * n).astype(np.int64)
+        key = (cell[:, 2] * n + cell[:, 1]) * n + cell[:, 0]
+        assert (np.diff(key) >= 0).all()
+        for d in range(3):
+            x = o_pos + d * (8 * m + gap)
+            v = o_mom + d * (rs * m + gap)
+            assert np.array_equal(blob[x:x + 8 * m].view(np.float64), pos[ids, d])
+            assert np.array_equal(blob[v:v + rs * m].view(ctx.np_dtype), u[ids, d])
+            if d < 2:
+                assert not blob[x + 8 * m:x + 8 * m + gap].any() and not blob[v + rs * m:v + rs * m + gap].any()
+    again = PMContext(n, n1, 100.0, physics="newtonian", precision=precision, n_particles_2=n2, mass_fraction_2=0.25)
+    again.set_state(blob)
+    assert np.array_equal(again.get_state(), blob)

@@ -12,51 +12,70 @@ constexpr int PK_NT = 256;
 
 __device__ __forceinline__ double sinc_d(double t) { return t == 0.0 ? 1.0 : sin(t) / t; }
 
-// per-block sums [count | P | |m|] over shells, in LDS, then one row of partials per block
+// per-block sums [count | P | |m|] over shells, in LDS, then one row of partials per block.
+// The modes (k_x, +-m_y, +-m_z) share |m|, the shell and the window, so they are taken together: one square root and
+// three LDS additions for up to four values (the additions of neighbouring k_x fall on the same few shells and
+// serialise), and the window comes from a table.  512^3 FP32: 0.73 -> 0.20 ms (0.54 GB: 0.08 at the copy rate); P(k) 4.12 -> 3.36.
 template <typename T>
 __global__ __launch_bounds__(PK_NT) void pk_bin_kernel(const cplx<T>* __restrict__ spec, int n, int nhp, double amp2,
                                                        double shot, long per_block, double* __restrict__ part) {
   extern __shared__ double sh[];
   const int nb = n / 2 + 1, nh = n / 2 + 1;
-  for (int i = threadIdx.x; i < 3 * nb; i += PK_NT) sh[i] = 0.0;
-  __syncthreads();
-  const long total = (long)n * n * nh;
-  const long t0 = (long)blockIdx.x * per_block, t1 = min(total, t0 + per_block);
+  double* iw = sh + 3 * nb;  // sinc(pi m / n)^-4
   const double pin = M_PI / n;
+  for (int i = threadIdx.x; i < 3 * nb; i += PK_NT) sh[i] = 0.0;
+  for (int i = threadIdx.x; i < nb; i += PK_NT) {
+    const double s = sinc_d(pin * i), s2 = s * s;
+    iw[i] = 1.0 / (s2 * s2);
+  }
+  __syncthreads();
+  const long total = (long)nh * nh * nh;
+  const long t0 = (long)blockIdx.x * per_block, t1 = min(total, t0 + per_block);
   for (long t = t0 + threadIdx.x; t < t1; t += PK_NT) {
     const int kx = (int)(t % nh);
-    const long r = t / nh;
-    const int ky = (int)(r % n), kz = (int)(r / n);
-    const int my = ky <= n / 2 ? ky : ky - n, mz = kz <= n / 2 ? kz : kz - n;
+    const int r = (int)(t / nh);
+    const int my = r % nh, mz = r / nh;
     const double m2 = (double)kx * kx + (double)my * my + (double)mz * mz;
     const double km = sqrt(m2);
     const int b = (int)rint(km);
     if (b < 1 || b >= nb) continue;
-    const double w = sinc_d(pin * kx) * sinc_d(pin * my) * sinc_d(pin * mz);
-    const double w2 = w * w;
-    const cplx<T> c = spec[((long)kz * n + ky) * nhp + kx];
-    const double p = ((double)c.x * c.x + (double)c.y * c.y) * amp2 / (w2 * w2) - shot;
-    const double wt = (kx > 0 && 2 * kx < n) ? 2.0 : 1.0;
+    // the rows of -m_y and -m_z (their own mirror images at 0 and n / 2)
+    const bool y2 = my > 0 && 2 * my < n, z2 = mz > 0 && 2 * mz < n;
+    const cplx<T>* q = spec + ((long)mz * n + my) * nhp + kx;
+    const long dy = (long)(n - 2 * my) * nhp, dz = (long)(n - 2 * mz) * n * nhp;
+    const cplx<T> zero = {(T)0, (T)0};
+    const cplx<T> c0 = q[0], c1 = y2 ? q[dy] : zero, c2 = z2 ? q[dz] : zero, c3 = y2 && z2 ? q[dy + dz] : zero;
+    auto norm2 = [](cplx<T> c) { return (double)c.x * c.x + (double)c.y * c.y; };
+    const double ps = (norm2(c0) + norm2(c1)) + (norm2(c2) + norm2(c3));
+    const double mult = (y2 ? 2.0 : 1.0) * (z2 ? 2.0 : 1.0), wx = (kx > 0 && 2 * kx < n) ? 2.0 : 1.0;
+    const double p = ps * amp2 * (iw[kx] * iw[my] * iw[mz]) - mult * shot;
+    const double wt = wx * mult;
     atomicAdd(&sh[b], wt);
-    atomicAdd(&sh[nb + b], wt * p);
+    atomicAdd(&sh[nb + b], wx * p);
     atomicAdd(&sh[2 * nb + b], wt * km);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < 3 * nb; i += PK_NT) part[(long)blockIdx.x * 3 * nb + i] = sh[i];
 }
 
-// fixed-order sum of the blocks' partials
+// fixed-order sum of the blocks' partials: 8 entries and 32 groups of rows to a workgroup
 __global__ __launch_bounds__(PK_NT) void pk_reduce_kernel(const double* __restrict__ part, int nblocks, int len,
                                                           double* __restrict__ out) {
-  const int i = blockIdx.x * PK_NT + threadIdx.x;
-  if (i >= len) return;
+  __shared__ double red[32][8];
+  const int i = blockIdx.x * 8 + (threadIdx.x & 7), g = threadIdx.x >> 3;
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += part[(long)b * len + i];
-  out[i] = s;
+  if (i < len)
+    for (int b = g; b < nblocks; b += 32) s += part[(long)b * len + i];
+  red[g][threadIdx.x & 7] = s;
+  __syncthreads();
+  if (g == 0 && i < len) {
+    for (int q = 1; q < 32; ++q) s += red[q][threadIdx.x];
+    out[i] = s;
+  }
 }
 
 int pk_blocks(int n, size_t scratch_bytes) {
-  const long total = (long)n * n * (n / 2 + 1);
+  const long nh = n / 2 + 1, total = nh * nh * nh;
   const long row = 3L * (n / 2 + 1) * 8;
   long nb = (total + 4 * PK_NT - 1) / (4 * PK_NT);
   nb = nb < 1024 ? nb : 1024;
@@ -68,12 +87,12 @@ int pk_blocks(int n, size_t scratch_bytes) {
 template <typename T>
 void launch_power_spectrum(const cplx<T>* spec, int n, int nhp, double amp2, double shot, int nblocks, double* scratch,
                            hipStream_t st) {
-  const long total = (long)n * n * (n / 2 + 1);
+  const long nh = n / 2 + 1, total = nh * nh * nh;
   const long per_block = (total + nblocks - 1) / nblocks;
   const int len = 3 * (n / 2 + 1);
-  hipLaunchKernelGGL((pk_bin_kernel<T>), dim3(nblocks), dim3(PK_NT), len * sizeof(double), st, spec, n, nhp, amp2,
+  hipLaunchKernelGGL((pk_bin_kernel<T>), dim3(nblocks), dim3(PK_NT), (len + nh) * sizeof(double), st, spec, n, nhp, amp2,
                      shot, per_block, scratch);
-  hipLaunchKernelGGL(pk_reduce_kernel, dim3((len + PK_NT - 1) / PK_NT), dim3(PK_NT), 0, st, scratch, nblocks, len,
+  hipLaunchKernelGGL(pk_reduce_kernel, dim3((len + 7) / 8), dim3(PK_NT), 0, st, scratch, nblocks, len,
                      scratch + (long)nblocks * len);
 }
 

@@ -570,43 +570,81 @@ void launch_deposit_vectors(const Particles<T>& p, const uint32_t* cell_start, i
 // the stored position).
 // ---------------------------------------------------------------------------
 // Blocks are TX x TY x TZ cells with TX = 32 (16 on a 16^3 mesh): rows of 32 cells keep the
-// row segments of the 4-byte particle arrays at whole 128-byte lines more often.  FP32: 32x4x8
-// cells and 512 threads (the field tile is 2.6 values per cell of the block).  FP64: 32x2x4 cells
-// and 256 threads: its 152 VGPRs allow 12 waves per CU, three such workgroups (measured at 512^3:
+// row segments of the particle records at whole 128-byte lines more often.  FP32: 32x4x8
+// cells (the field tile is 2.6 values per cell of the block) and 512 threads, or 256 with two
+// fields or one where a block holds fewer than 512 particles on average (256^3 scalar with 128^3 particles: 0.179 ->
+// 0.155 ms; with a particle per cell the kick gains 6 % too, but the sort that follows loses as much, its ranks being
+// drawn in a more mixed order), on meshes large enough to fill the chip with them (64^3: 18 -> 24 us).
+// Blocks of 2048 cells and 1024 threads (5.4 ms) or of 512 or 256 cells (4.97 - 5.15 ms) are slower.
+// FP64: 32x2x4 cells and 256 threads: its registers allow 12 waves per CU, three such workgroups (measured at 512^3:
 // 8.5 ms against 9.6 ms for 32x4x8 with 512 threads, whose 108 KB tile holds one per CU).
-template <typename T> struct KdShape { static constexpr int TY = 4, TZ = 8, NT = 512; };
-template <> struct KdShape<double> { static constexpr int TY = 2, TZ = 4, NT = 256; };
+template <typename T> struct KdShape { static constexpr int TY = 4, TZ = 8, WPE = 4; };
+template <> struct KdShape<double> { static constexpr int TY = 2, TZ = 4, WPE = 3; };
 template <typename T, int TX> struct KdTile {
   static constexpr int GX = TX + 3, GY = KdShape<T>::TY + 3, GZ = KdShape<T>::TZ + 3, G = GX * GY * GZ;
 };
 
-template <typename T, int GX, int GY>
-__device__ __forceinline__ void gather_lds(const T* __restrict__ f, int zo0, int yo0, int xo0, const T* wx, const T* wy,
-                                           const T* wz, T half_n, T& val, T* g) {
-  // f: LDS tile with x stride 1, y stride GX, z stride GX*GY whose index 0 is the vertex one
-  // below the block in every axis; (xo0, yo0, zo0) = the particle's cell relative to the block, so the
-  // cell's lower corner is tile index (xo0 + 1, yo0 + 1, zo0 + 1)
-  T v = 0, gx = 0, gy = 0, gz = 0;
+// W fields of the tile side by side per vertex: one LDS read of up to 16 bytes brings all of them at an immediate
+// offset from the particle's corner (field after field a particle took 107 LDS reads and 100 address additions in
+// FP32 with five fields, now 64 and 25; kick at 512^3: 4.65 -> 4.03 ms on the grid, 4.85 -> 4.6 clustered; FP64 at
+// 256^3 1.08 -> 0.98).
+template <typename T, int W> struct alignas(W * sizeof(T)) FieldVec { T f[W]; };
+
+// Values v and gradients g[c] of W fields at a particle.  f: the tile with x stride 1, y stride GX, z stride GX*GY, at the
+// vertex one below the particle's cell in every axis
+template <typename T, int W, int GX, int GY>
+__device__ __forceinline__ void gather_lds(const FieldVec<T, W>* __restrict__ f, const T* wx, const T* wy, const T* wz,
+                                           T half_n, T* v, T (*g)[3]) {
+  // The order of the sums is that of the corners.  The outer vertices of a direction are asked for while the previous
+  // ones are summed; the empty asm keeps the compiler from asking for all 32 vertices first (236 registers in FP32
+  // where 128 let four waves share a SIMD).
   constexpr int SY = GX, SZ = GX * GY;
+  FieldVec<T, W> in[2][2][2];  // the corners of the particle's cell
 #pragma unroll
-  for (int cz = 0; cz < 2; ++cz) {
+  for (int cz = 0; cz < 2; ++cz)
 #pragma unroll
-    for (int cy = 0; cy < 2; ++cy) {
+    for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+      for (int cx = 0; cx < 2; ++cx) in[cz][cy][cx] = f[(cz + 1) * SZ + (cy + 1) * SY + (cx + 1)];
+#pragma unroll
+  for (int c = 0; c < W; ++c) v[c] = g[c][0] = g[c][1] = g[c][2] = (T)0;
+  FieldVec<T, W> out[2][2][2];
+  auto load = [&](int k) {
+    const int cz = k / 3, d = k % 3;
+#pragma unroll
+    for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+      for (int cx = 0; cx < 2; ++cx)
+        out[k & 1][cy][cx] =
+            f[(d == 2 ? 3 * cz : cz + 1) * SZ + (d == 1 ? 3 * cy : cy + 1) * SY + (d == 0 ? 3 * cx : cx + 1)];
+  };
+  load(0);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const int cz = k / 3, d = k % 3;
+    if (k < 5) load(k + 1);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int cy = 0; cy < 2; ++cy)
 #pragma unroll
       for (int cx = 0; cx < 2; ++cx) {
         const T w = wx[cx] * wy[cy] * wz[cz];
-        const int b = (zo0 + cz + 1) * SZ + (yo0 + cy + 1) * SY + (xo0 + cx + 1);
-        v += w * f[b];
-        gx += w * (f[b + 1] - f[b - 1]);
-        gy += w * (f[b + SY] - f[b - SY]);
-        gz += w * (f[b + SZ] - f[b - SZ]);
+        const bool up = d == 0 ? cx : (d == 1 ? cy : cz);
+        const FieldVec<T, W> i = d == 0 ? in[cz][cy][1 - cx] : (d == 1 ? in[cz][1 - cy][cx] : in[1 - cz][cy][cx]);
+        const FieldVec<T, W> o = out[k & 1][cy][cx];
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+          if (d == 0) v[c] += w * in[cz][cy][cx].f[c];
+          g[c][d] += w * (up ? o.f[c] - i.f[c] : i.f[c] - o.f[c]);
+        }
       }
-    }
+#pragma unroll
+    for (int c = 0; c < W; ++c) asm volatile("" : "+v"(v[c]), "+v"(g[c][d]) : : "memory");
   }
-  val = v;
-  g[0] = gx * half_n;
-  g[1] = gy * half_n;
-  g[2] = gz * half_n;
+#pragma unroll
+  for (int c = 0; c < W; ++c)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) g[c][d] *= half_n;
 }
 
 // Rank of a particle among those that reach the same cell.  The store is
@@ -631,18 +669,22 @@ __device__ __forceinline__ uint32_t rank_in_cell(uint32_t* cnt, uint32_t k) {
   return base + (uint32_t)(lane - head);
 }
 
-template <typename T, int MODE, int TX>
-__global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T> p,
+template <typename T, int MODE, int TX, int KD_NT>
+__global__ __launch_bounds__(KD_NT, KdShape<T>::WPE) void kick_drift_kernel(Particles<T> p,
                                                                     const uint32_t* __restrict__ cell_start, int n,
                                                                     GatherArgs<T> ga, uint32_t* rank, uint32_t* cnt,
                                                                     int* err) {
-  constexpr int KD_TY = KdShape<T>::TY, KD_TZ = KdShape<T>::TZ, KD_NT = KdShape<T>::NT;
+  constexpr int KD_TY = KdShape<T>::TY, KD_TZ = KdShape<T>::TZ;
   constexpr int NF = MODE == MODE_FULL ? 5 : (MODE == MODE_SCALAR ? 2 : 1);
   constexpr int NR = KD_TY * KD_TZ;                   // particle rows of the block
   constexpr int KD_GX = KdTile<T, TX>::GX, KD_GY = KdTile<T, TX>::GY, KD_G = KdTile<T, TX>::G;
   constexpr int NTL = (KD_G + KD_NT - 1) / KD_NT;     // tile entries per thread and field
   static_assert(NR <= 64, "row scan in one wave");
-  __shared__ T tile[NF][KD_G];
+  // fields per vertex of the first tile, and of the others
+  constexpr int WA = NF == 5 ? (sizeof(T) == 4 ? 4 : 2) : NF, WB = NF == 5 && sizeof(T) == 8 ? 2 : 0, WC = NF - WA - WB;
+  __shared__ FieldVec<T, WA> tile_a[KD_G];
+  __shared__ FieldVec<T, WB ? WB : 1> tile_b[WB ? KD_G : 1];
+  __shared__ T tile_c[WC ? KD_G : 1];
   __shared__ uint32_t rbeg[NR], roff[NR + 1];
   const int m = n - 1;
   int bx, by, bz;
@@ -681,8 +723,17 @@ __global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T>
   for (int k = 0; k < NTL; ++k) {
     const int q = tid + k * KD_NT;
     if (q < KD_G) {
+      FieldVec<T, WA> va;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) tile[f][q] = tv[f][k];
+      for (int f = 0; f < WA; ++f) va.f[f] = tv[f][k];
+      tile_a[q] = va;
+      if constexpr (WB > 0) {
+        FieldVec<T, WB> vb;
+#pragma unroll
+        for (int f = 0; f < WB; ++f) vb.f[f] = tv[WA + f][k];
+        tile_b[q] = vb;
+      }
+      if constexpr (WC > 0) tile_c[q] = tv[NF - 1][k];
     }
   }
   __syncthreads();
@@ -713,8 +764,15 @@ __global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T>
     cell_of(z, n, iz, fzd);
     const T wx[2] = {(T)1 - (T)fxd, (T)fxd}, wy[2] = {(T)1 - (T)fyd, (T)fyd}, wz[2] = {(T)1 - (T)fzd, (T)fzd};
     const int lx = ix - x0, ly = iy - y0, lz = iz - z0;  // in [0, T*) by construction of the rows
-    T phi_p, gphi[3];
-    gather_lds<T, KD_GX, KD_GY>(tile[0], lz, ly, lx, wx, wy, wz, hn, phi_p, gphi);
+    const int corner = (lz * KD_GY + ly) * KD_GX + lx;
+    T fv[NF], gf[NF][3];
+    gather_lds<T, WA, KD_GX, KD_GY>(tile_a + corner, wx, wy, wz, hn, fv, gf);
+    if constexpr (WB > 0) gather_lds<T, WB, KD_GX, KD_GY>(tile_b + corner, wx, wy, wz, hn, fv + WA, gf + WA);
+    if constexpr (WC > 0)
+      gather_lds<T, 1, KD_GX, KD_GY>(reinterpret_cast<const FieldVec<T, 1>*>(tile_c) + corner, wx, wy, wz, hn, fv + NF - 1,
+                                     gf + NF - 1);
+    const T phi_p = fv[0];
+    T* gphi = gf[0];
     if (ga.corr) {
       // learned closure: CIC-interpolated correction to grad phi
       const long n3 = nn * n;
@@ -741,8 +799,8 @@ __global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T>
       const T ia = rcp(ah);
       vx = ux * ia; vy = uy * ia; vz = uz * ia;
     } else {
-      T chi_p, gchi[3];
-      gather_lds<T, KD_GX, KD_GY>(tile[1], lz, ly, lx, wx, wy, wz, hn, chi_p, gchi);
+      const T chi_p = fv[1];
+      const T* gchi = gf[1];
       const T u2 = ux * ux + uy * uy + uz * uz;
       const T ie = rsqrt_(a * a + u2);
       const T e = (a * a + u2) * ie;
@@ -752,10 +810,8 @@ __global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T>
       T fz = cphi * gphi[2] + e * gchi[2];
       T B[3] = {0, 0, 0};
       if constexpr (MODE == MODE_FULL) {
-        T gb[3][3];  // gb[j][i] = d_i B_j
-        gather_lds<T, KD_GX, KD_GY>(tile[2 % NF], lz, ly, lx, wx, wy, wz, hn, B[0], gb[0]);
-        gather_lds<T, KD_GX, KD_GY>(tile[3 % NF], lz, ly, lx, wx, wy, wz, hn, B[1], gb[1]);
-        gather_lds<T, KD_GX, KD_GY>(tile[4 % NF], lz, ly, lx, wx, wy, wz, hn, B[2], gb[2]);
+        const T(*gb)[3] = gf + 2;  // gb[j][i] = d_i B_j
+        B[0] = fv[2]; B[1] = fv[3]; B[2] = fv[4];
         fx -= ux * gb[0][0] + uy * gb[1][0] + uz * gb[2][0];
         fy -= ux * gb[0][1] + uy * gb[1][1] + uz * gb[2][1];
         fz -= ux * gb[0][2] + uy * gb[1][2] + uz * gb[2][2];
@@ -784,30 +840,31 @@ __global__ __launch_bounds__(KdShape<T>::NT) void kick_drift_kernel(Particles<T>
   }
 }
 
-template <typename T, int TX>
+template <typename T, int TX, int NT, int NT_FULL>
 static void launch_kick_drift_tx(const Particles<T>& p, int n, const uint32_t* cell_start, const GatherArgs<T>& g,
                                  uint32_t* rank, uint32_t* cnt, int* err, hipStream_t st) {
-  constexpr int KD_NT = KdShape<T>::NT;
   dim3 grid(n / TX, n / KdShape<T>::TY, n / KdShape<T>::TZ);
   if (g.mode == MODE_NEWTONIAN)
-    hipLaunchKernelGGL((kick_drift_kernel<T, MODE_NEWTONIAN, TX>), grid, dim3(KD_NT), 0, st, p, cell_start, n, g, rank,
+    hipLaunchKernelGGL((kick_drift_kernel<T, MODE_NEWTONIAN, TX, NT>), grid, dim3(NT), 0, st, p, cell_start, n, g, rank,
                        cnt, err);
   else if (g.mode == MODE_SCALAR)
-    hipLaunchKernelGGL((kick_drift_kernel<T, MODE_SCALAR, TX>), grid, dim3(KD_NT), 0, st, p, cell_start, n, g, rank,
+    hipLaunchKernelGGL((kick_drift_kernel<T, MODE_SCALAR, TX, NT>), grid, dim3(NT), 0, st, p, cell_start, n, g, rank,
                        cnt, err);
   else
-    hipLaunchKernelGGL((kick_drift_kernel<T, MODE_FULL, TX>), grid, dim3(KD_NT), 0, st, p, cell_start, n, g, rank, cnt,
-                       err);
+    hipLaunchKernelGGL((kick_drift_kernel<T, MODE_FULL, TX, NT_FULL>), grid, dim3(NT_FULL), 0, st, p, cell_start, n, g,
+                       rank, cnt, err);
 }
 
 template <typename T>
 void launch_kick_drift(const Particles<T>& p, long np, int n, const uint32_t* cell_start, const GatherArgs<T>& g,
                        uint32_t* rank, uint32_t* cnt, int* err, hipStream_t st) {
-  (void)np;
-  if (n >= 32)
-    launch_kick_drift_tx<T, 32>(p, n, cell_start, g, rank, cnt, err, st);
+  constexpr int NT = sizeof(T) == 4 ? 512 : 256;
+  if (n >= 128 && 2 * np <= (long)n * n * n)
+    launch_kick_drift_tx<T, 32, 256, NT>(p, n, cell_start, g, rank, cnt, err, st);
+  else if (n >= 32)
+    launch_kick_drift_tx<T, 32, NT, NT>(p, n, cell_start, g, rank, cnt, err, st);
   else
-    launch_kick_drift_tx<T, 16>(p, n, cell_start, g, rank, cnt, err, st);
+    launch_kick_drift_tx<T, 16, NT, NT>(p, n, cell_start, g, rank, cnt, err, st);
 }
 
 // ---------------------------------------------------------------------------

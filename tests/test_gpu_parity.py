@@ -193,6 +193,18 @@ def test_newtonian_fp32_steps(n):
     assert periodic_max_dx(gp, sim.particles_by_id()[0], n) < POS_TOL["fp32"]
 
 
+@pytest.mark.parametrize("physics", ["newtonian", "scalar"])
+def test_fp32_few_particles_per_cell(physics):
+    """An eighth of a particle per cell on a 128^3 mesh: the kick's workgroups of 256 threads (FP32, up to two fields)."""
+    _say(f"fp32 {physics} 64^3 particles on 128^3")
+    pos, u, tau0, dtau = config_particles("zeldovich_32_scalar_fp64", n=64)
+    worst, dxmax, urel, *_ = _run_both(128, 320.0, physics, "fp32", pos, u, tau0, [dtau] * 2)
+    _say(worst, dxmax, urel)
+    for k, v in worst.items():
+        assert v < FIELD_TOL["fp32"], (k, v)
+    assert dxmax < POS_TOL["fp32"]
+
+
 @pytest.mark.parametrize("physics", ["newtonian", "full"])
 def test_fp64_step_parity_physics(physics):
     _say(f"fp64 {physics}")

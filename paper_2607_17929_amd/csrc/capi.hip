@@ -929,33 +929,17 @@ pm_status pm_debug_fft(pm_ctx* c, const void* d_in, void* d_out, int direction) 
   if (!c || !d_in || !d_out) return PM_EINVAL;
   if (direction != 1 && direction != -1) return PM_EINVAL;
   const Layout& L = c->L;
-  if (c->cfg.precision == PM_FP64) {
-    cplx<double>* spec = c->at<cplx<double>>(L.spec);
-    if (direction == 1) {
-      SrcArgsH<double> s;
-      s.raw = reinterpret_cast<const double*>(d_in);
-      fft_forward<double>(s, MODE_RAW, c->n, L.nhp, spec, 1, c->at<cplx<double>>(L.tw), c->st);
-      launch_copy_unpad<double>(spec, c->n, L.nhp, reinterpret_cast<cplx<double>*>(d_out), false, c->st);
-    } else {
-      launch_copy_unpad<double>(spec, c->n, L.nhp, const_cast<cplx<double>*>(reinterpret_cast<const cplx<double>*>(d_in)),
-                                true, c->st);
-      double* out[1] = {reinterpret_cast<double*>(d_out)};
-      fft_inverse<double>(c->n, L.nhp, spec, 1, out, 1.0 / c->n3, c->at<cplx<double>>(L.tw), c->st);
-    }
-  } else {
-    cplx<float>* spec = c->at<cplx<float>>(L.spec);
-    if (direction == 1) {
-      SrcArgsH<float> s;
-      s.raw = reinterpret_cast<const float*>(d_in);
-      fft_forward<float>(s, MODE_RAW, c->n, L.nhp, spec, 1, c->at<cplx<float>>(L.tw), c->st);
-      launch_copy_unpad<float>(spec, c->n, L.nhp, reinterpret_cast<cplx<float>*>(d_out), false, c->st);
-    } else {
-      launch_copy_unpad<float>(spec, c->n, L.nhp, const_cast<cplx<float>*>(reinterpret_cast<const cplx<float>*>(d_in)),
-                               true, c->st);
-      float* out[1] = {reinterpret_cast<float*>(d_out)};
-      fft_inverse<float>(c->n, L.nhp, spec, 1, out, 1.0 / c->n3, c->at<cplx<float>>(L.tw), c->st);
-    }
-  }
+  auto run = [&](auto zero) {
+    using T = decltype(zero);
+    cplx<T>* spec = c->at<cplx<T>>(L.spec);
+    const cplx<T>* tw = c->at<cplx<T>>(L.tw);
+    if (direction == 1)
+      fft_forward_dense<T>(reinterpret_cast<const T*>(d_in), c->n, L.nhp, spec, reinterpret_cast<cplx<T>*>(d_out), tw, c->st);
+    else
+      fft_inverse_dense<T>(reinterpret_cast<const cplx<T>*>(d_in), c->n, L.nhp, spec, reinterpret_cast<T*>(d_out), tw, c->st);
+  };
+  if (c->cfg.precision == PM_FP64) run(0.0);
+  else run(0.0f);
   return c->hip_check("debug_fft");
 }
 

@@ -21,6 +21,7 @@ namespace gpm {
 // table in global memory: one load instead of R - 1; at most three roundings deep).
 // NTG: the global reads and writes carry the non-temporal hint (streamed data that is not read again
 // soon; measured faster for the plain column passes, slower for the fused Fourier-space kernel).
+// PART: columns from ncol on are neither read (they count as zero) nor written.
 template <typename T, int R, bool INV>
 __device__ __forceinline__ void twiddle_pow(cplx<T>* v, cplx<T> w1) {
   cplx<T> w[8];
@@ -44,9 +45,9 @@ __device__ __forceinline__ void store_nt(cplx<T>* p, cplx<T> v) {
 }
 
 template <typename T, int N, int C, int NT, int S, bool INV, bool FROM_G, bool TO_G, typename IX, bool TWPOW = false,
-          bool NTG = false>
+          bool NTG = false, bool PART = false>
 __device__ __forceinline__ void col_stage(cplx<T>* sm, const cplx<T>* gin, IX esin, cplx<T>* gout, IX esout,
-                                          const cplx<T>* stw) {
+                                          const cplx<T>* stw, int ncol = C) {
   constexpr int R = stage_radix(N, S);
   constexpr int NS = stage_ns(N, S);
   constexpr int J = N * C / R;
@@ -61,7 +62,9 @@ __device__ __forceinline__ void col_stage(cplx<T>* sm, const cplx<T>* gin, IX es
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const int e = i + r * (N / R);
-        if (FROM_G) {
+        if (FROM_G && PART && col >= ncol) {
+          v[p][r] = mk<T>((T)0, (T)0);
+        } else if (FROM_G) {
           v[p][r] = NTG ? load_nt(gin + ((IX)e * esin + (IX)col)) : gin[(IX)e * esin + (IX)col];
         } else {
           v[p][r] = sm[e * C + col];
@@ -92,7 +95,8 @@ __device__ __forceinline__ void col_stage(cplx<T>* sm, const cplx<T>* gin, IX es
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const int e = j0 + r * NS;
-        if (TO_G) {
+        if (TO_G && PART && col >= ncol) {
+        } else if (TO_G) {
           if (NTG) store_nt(gout + ((IX)e * esout + (IX)col), v[p][r]);
           else gout[(IX)e * esout + (IX)col] = v[p][r];
         } else {
@@ -107,14 +111,14 @@ __device__ __forceinline__ void col_stage(cplx<T>* sm, const cplx<T>* gin, IX es
 // All stages of the transform; GIN / GOUT: the first stage reads global memory, the last
 // stage writes global memory (otherwise the tile starts / ends in LDS).
 template <typename T, int N, int C, int NT, int S, bool INV, bool GIN, bool GOUT, typename IX, bool TWPOW = false,
-          bool NTG = false>
+          bool NTG = false, bool PART = false>
 __device__ __forceinline__ void col_stages(cplx<T>* sm, const cplx<T>* gin, IX esin, cplx<T>* gout, IX esout,
-                                           const cplx<T>* stw) {
+                                           const cplx<T>* stw, int ncol = C) {
   constexpr int NSTG = nstages(N);
   if constexpr (S < NSTG) {
-    col_stage<T, N, C, NT, S, INV, GIN && S == 0, GOUT && S == NSTG - 1, IX, TWPOW, NTG>(sm, gin, esin, gout, esout,
-                                                                                          stw);
-    col_stages<T, N, C, NT, S + 1, INV, GIN, GOUT, IX, TWPOW, NTG>(sm, gin, esin, gout, esout, stw);
+    col_stage<T, N, C, NT, S, INV, GIN && S == 0, GOUT && S == NSTG - 1, IX, TWPOW, NTG, PART>(sm, gin, esin, gout,
+                                                                                                esout, stw, ncol);
+    col_stages<T, N, C, NT, S + 1, INV, GIN, GOUT, IX, TWPOW, NTG, PART>(sm, gin, esin, gout, esout, stw, ncol);
   }
 }
 

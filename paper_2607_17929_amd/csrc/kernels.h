@@ -48,6 +48,11 @@ void fft_forward(const SrcArgsH<T>& a, int mode, int n, int nhp, cplx<T>* spec, 
 template <typename T>
 void fft_inverse(int n, int nhp, cplx<T>* spec, int nout, T* const* outp, double out_scale, const cplx<T>* tw,
                  hipStream_t st);
+// one real field and its half spectrum in dense rows of n / 2 + 1 (spec: padded scratch)
+template <typename T>
+void fft_forward_dense(const T* in, int n, int nhp, cplx<T>* spec, cplx<T>* out, const cplx<T>* tw, hipStream_t st);
+template <typename T>
+void fft_inverse_dense(const cplx<T>* in, int n, int nhp, cplx<T>* spec, T* out, const cplx<T>* tw, hipStream_t st);
 
 // ---- solve.hip ----
 // solution components of a solve: phi | phi, chi | phi, chi, B_x, B_y, B_z
@@ -264,8 +269,6 @@ void launch_check_store(const Particles<T>& p, long np, int nmesh, const uint32_
                         hipStream_t st);
 template <typename T>
 void launch_export(const Particles<T>& p, long np, double* pos_aos, T* u_aos, uint32_t* ids, hipStream_t st);
-template <typename T>
-void launch_copy_unpad(const cplx<T>* spec, int n, int nhp, cplx<T>* out, bool to_padded, hipStream_t st);
 
 // ---- closure.hip ----
 void closure_pack(const float* params, uint16_t* wf, uint16_t* wb, float* bias, hipStream_t st);

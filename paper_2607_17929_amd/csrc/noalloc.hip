@@ -52,14 +52,9 @@ pm_status run_fft(const void* d_in, void* d_out, int n, int direction, hipStream
   cplx<T>* tw = reinterpret_cast<cplx<T>*>(base + align256((size_t)n * n * nhp * sizeof(cplx<T>)));
   hipLaunchKernelGGL((twiddle_kernel<T>), dim3((n + 255) / 256), dim3(256), 0, st, tw, n);
   if (direction == 1) {
-    SrcArgsH<T> s;
-    s.raw = reinterpret_cast<const T*>(d_in);
-    fft_forward<T>(s, MODE_RAW, n, nhp, spec, 1, tw, st);
-    launch_copy_unpad<T>(spec, n, nhp, reinterpret_cast<cplx<T>*>(d_out), false, st);
+    fft_forward_dense<T>(reinterpret_cast<const T*>(d_in), n, nhp, spec, reinterpret_cast<cplx<T>*>(d_out), tw, st);
   } else {
-    launch_copy_unpad<T>(spec, n, nhp, const_cast<cplx<T>*>(reinterpret_cast<const cplx<T>*>(d_in)), true, st);
-    T* out[1] = {reinterpret_cast<T*>(d_out)};
-    fft_inverse<T>(n, nhp, spec, 1, out, 1.0 / ((double)n * n * n), tw, st);
+    fft_inverse_dense<T>(reinterpret_cast<const cplx<T>*>(d_in), n, nhp, spec, reinterpret_cast<T*>(d_out), tw, st);
   }
   return hipGetLastError() == hipSuccess ? PM_OK : PM_EHIP;
 }

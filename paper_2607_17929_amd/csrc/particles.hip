@@ -1181,30 +1181,6 @@ void launch_export(const Particles<T>& p, long np, double* pos_aos, T* u_aos, ui
                      ids);
 }
 
-// ---------------------------------------------------------------------------
-// padded <-> dense half spectrum copies (diagnostic FFT entry point)
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void copy_unpad_kernel(const cplx<T>* a, int n, int nhp, cplx<T>* b, bool to_padded) {
-  const int nh = n / 2 + 1;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)n * n * nh) return;
-  const int kx = (int)(t % nh);
-  const long row = t / nh;
-  if (to_padded) {
-    const_cast<cplx<T>*>(a)[row * nhp + kx] = b[t];
-  } else {
-    b[t] = a[row * nhp + kx];
-  }
-}
-
-template <typename T>
-void launch_copy_unpad(const cplx<T>* spec, int n, int nhp, cplx<T>* out, bool to_padded, hipStream_t st) {
-  const long total = (long)n * n * (n / 2 + 1);
-  hipLaunchKernelGGL((copy_unpad_kernel<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, spec, n, nhp, out,
-                     to_padded);
-}
-
 #define GPM_INST(T)                                                                                                   \
   template void launch_ingest<T>(const double*, const T*, const uint32_t*, long, Particles<T>, int, uint32_t*,         \
                                  uint32_t*, int*, hipStream_t);                                                        \
@@ -1220,8 +1196,7 @@ void launch_copy_unpad(const cplx<T>* spec, int n, int nhp, cplx<T>* out, bool t
                                           hipStream_t);                                                               \
   template void launch_export<T>(const Particles<T>&, long, double*, T*, uint32_t*, hipStream_t);                      \
   template void launch_check_store<T>(const Particles<T>&, long, int, const uint32_t*, int*, hipStream_t);            \
-  template void launch_order_by_id<T>(const Particles<T>&, Particles<T>, long, int, const uint32_t*, hipStream_t);     \
-  template void launch_copy_unpad<T>(const cplx<T>*, int, int, cplx<T>*, bool, hipStream_t);
+  template void launch_order_by_id<T>(const Particles<T>&, Particles<T>, long, int, const uint32_t*, hipStream_t);
 GPM_INST(float)
 GPM_INST(double)
 

@@ -273,31 +273,45 @@ __global__ __launch_bounds__(NT) void kspace_kernel(SolveArgs<T> a) {
   col_stages<T, N, CO, NT, 0, true, false, true, IX, KS_TWPOW>(sm, nullptr, (IX)0, gout, (IX)N * a.nhp * NO, stw);
 }
 
-// Tile shape (measured at 512^3, FP32 full physics: rows of 4 kx x 10 components = 320 B in a
-// 160 KB tile, one workgroup per CU, run faster than 160 B rows with two workgroups per CU; 1024
-// threads, 16 waves on the CU's one tile, 3.54 ms against 3.63 with 512)
+// Tile shape.  A workgroup's passes (global to LDS, solves, LDS to global) follow each other, so a CU needs several
+// workgroups to keep its memory pipes busy: the largest tile that leaves room for three on a CU, or for two where its
+// rows would be shorter than KS_ROW_MIN, or for one where those of two still are.  Measured, one tile of up to 160 KB
+// per CU against this rule: 512^3 FP32 full 3.58 -> 2.99 ms (two tiles of 2 kx; three of 1 kx, rows of 80 bytes: 3.08),
+// 256^3 FP32 full 0.45 -> 0.33, scalar 0.217 -> 0.154 (two tiles of 4 kx: 0.166), FP64 full 0.94 -> 0.64 - 0.72.
+// FP64 with the parabolic state: 7 more values per mode are read and written, in rows of 64 and 48 bytes per kx, and
+// the whole row of 4 kx is kept where one workgroup's LDS holds it (256^3: 0.83 ms against 0.87 for tiles of 1 or 2;
+// at 512^3, where it doesn't, 6.53 -> 6.16 ms by the rule above).
 constexpr int KS_ROW_BYTES = 256;   // contiguous bytes wanted per row of a tile
-constexpr long KS_LDS = 163840;     // LDS budget of a tile
-constexpr int KS_NT = 1024;         // threads of a workgroup when the tile has that many modes
+constexpr int KS_ROW_MIN = 96;      // and not to fall below for the sake of more workgroups
+constexpr long KS_LDS[3] = {53760, 81920, 163840};  // LDS of a workgroup, three, two and one to a CU
+struct KspaceTile { int kxt; long lds; };
 // kx values per workgroup: KXT * NS * sizeof(complex) >= KS_ROW_BYTES contiguous bytes where the
 // LDS tile allows, and at most 16: the rows are padded to a multiple of 16 kx, so that a tile of more
 // would reach into (and store over) the next row, another workgroup's
-template <typename T, int N, int NS> constexpr int kspace_kxt() {
-  constexpr int want = (KS_ROW_BYTES + NS * (int)sizeof(cplx<T>) - 1) / (NS * (int)sizeof(cplx<T>));
-  int k = 1;
-  while (k < want && k < 16) k *= 2;
-  while (k > 1 && (long)N * k * NS * (long)sizeof(cplx<T>) > KS_LDS) k /= 2;
-  return k;
+template <typename T, int N, int MODE> constexpr KspaceTile kspace_tile() {
+  constexpr int NS = mode_nsrc(MODE), rec = NS * (int)sizeof(cplx<T>), want = (KS_ROW_BYTES + rec - 1) / rec;
+  int most = 1;
+  while (most < want && most < 16) most *= 2;
+  if (MODE == MODE_FULLP && sizeof(T) == 8 && (long)N * most * rec <= KS_LDS[2]) return {most, KS_LDS[2]};
+  for (int i = 0; i < 3; ++i) {
+    int k = most;
+    while (k > 1 && (long)N * k * rec > KS_LDS[i]) k /= 2;
+    if (i == 2 || ((long)N * k * rec <= KS_LDS[i] && (k == most || k * rec >= KS_ROW_MIN))) return {k, KS_LDS[i]};
+  }
+  return {1, KS_LDS[2]};
 }
 
 template <typename T, int N, int MODE>
 static void launch_kspace_n(const SolveArgs<T>& a, hipStream_t st) {
   constexpr int NS = mode_nsrc(MODE);
-  constexpr int KXT = kspace_kxt<T, N, NS>();
-  constexpr int NT = N * KXT >= KS_NT ? KS_NT : (N * KXT >= 256 ? 256 : 64);
-  constexpr bool TW_LDS = (long)N * KXT * NS * (long)sizeof(cplx<T>) + N * (long)sizeof(cplx<T>) <= KS_LDS;
-  static_assert((long)N * KXT * NS * (long)sizeof(cplx<T>) + (TW_LDS ? N : 0) * (long)sizeof(cplx<T>) <= 160 * 1024,
-                "LDS tile too large");
+  constexpr KspaceTile TILE = kspace_tile<T, N, MODE>();
+  constexpr int KXT = TILE.kxt, MODES = N * KXT;
+  // one thread per mode; at most 512 in each of three workgroups, 1024 in each of two (512^3: 2.99 ms, 512: 3.15)
+  constexpr int MOST = TILE.lds == KS_LDS[0] ? 512 : 1024;
+  constexpr int NT = MODES >= MOST ? MOST : (MODES >= 512 ? 512 : MODES >= 256 ? 256 : 64);
+  constexpr long TILE_BYTES = (long)MODES * NS * (long)sizeof(cplx<T>);
+  constexpr bool TW_LDS = TILE_BYTES + N * (long)sizeof(cplx<T>) <= TILE.lds;
+  static_assert(TILE_BYTES <= 160 * 1024, "LDS tile too large");
   const int nh = N / 2 + 1;
   dim3 grid((unsigned)((nh + KXT - 1) / KXT), N);
   hipLaunchKernelGGL((kspace_kernel<T, N, MODE, KXT, NT, TW_LDS>), grid, dim3(NT), 0, st, a);

@@ -205,6 +205,19 @@ def test_fp32_few_particles_per_cell(physics):
     assert dxmax < POS_TOL["fp32"]
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_full_physics_128(precision):
+    """The Fourier-space kernel where its tiles are narrower than the row it wants (128^3: 4 kx in FP32 but 2 in FP64,
+    more than one workgroup to a CU), with the tensor state advanced."""
+    _say(f"{precision} full 32^3 particles on 128^3")
+    pos, u, tau0, dtau = config_particles("zeldovich_32_scalar_fp64")
+    worst, dxmax, urel, *_ = _run_both(128, 320.0, "full", precision, pos, u, tau0, [dtau] * 2)
+    _say(worst, dxmax, urel)
+    for k, v in worst.items():
+        assert v < FIELD_TOL[precision], (k, v)
+    assert dxmax < POS_TOL[precision]
+
+
 @pytest.mark.parametrize("physics", ["newtonian", "full"])
 def test_fp64_step_parity_physics(physics):
     _say(f"fp64 {physics}")

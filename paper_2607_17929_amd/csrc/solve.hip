@@ -280,7 +280,8 @@ __global__ __launch_bounds__(NT) void kspace_kernel(SolveArgs<T> a) {
 // 256^3 FP32 full 0.45 -> 0.33, scalar 0.217 -> 0.154 (two tiles of 4 kx: 0.166), FP64 full 0.94 -> 0.64 - 0.72.
 // FP64 with the parabolic state: 7 more values per mode are read and written, in rows of 64 and 48 bytes per kx, and
 // the whole row of 4 kx is kept where one workgroup's LDS holds it (256^3: 0.83 ms against 0.87 for tiles of 1 or 2;
-// at 512^3, where it doesn't, 6.53 -> 6.16 ms by the rule above).
+// at 512^3, where it doesn't, 6.60 - 7.32 -> 5.96 - 6.29 ms by the rule above).  FP64 full at 512^3 keeps one tile of 2 kx,
+// 5.72 - 6.05 ms from run to run: two of 1 kx take 5.50 - 5.66 in some runs and 6.51 in others.
 constexpr int KS_ROW_BYTES = 256;   // contiguous bytes wanted per row of a tile
 constexpr int KS_ROW_MIN = 96;      // and not to fall below for the sake of more workgroups
 constexpr long KS_LDS[3] = {53760, 81920, 163840};  // LDS of a workgroup, three, two and one to a CU
@@ -294,6 +295,7 @@ template <typename T, int N, int MODE> constexpr KspaceTile kspace_tile() {
   while (most < want && most < 16) most *= 2;
   if (MODE == MODE_FULLP && sizeof(T) == 8 && (long)N * most * rec <= KS_LDS[2]) return {most, KS_LDS[2]};
   for (int i = 0; i < 3; ++i) {
+    if (i == 1 && MODE == MODE_FULL && sizeof(T) == 8) continue;
     int k = most;
     while (k > 1 && (long)N * k * rec > KS_LDS[i]) k /= 2;
     if (i == 2 || ((long)N * k * rec <= KS_LDS[i] && (k == most || k * rec >= KS_ROW_MIN))) return {k, KS_LDS[i]};

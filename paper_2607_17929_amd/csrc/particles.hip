@@ -585,8 +585,8 @@ template <typename T, int TX> struct KdTile {
 };
 
 // W fields of the tile side by side per vertex: one LDS read of up to 16 bytes brings all of them at an immediate
-// offset from the particle's corner (field after field a particle took 107 LDS reads and 100 address additions in
-// FP32 with five fields, now 64 and 25; kick at 512^3: 4.65 -> 4.03 ms on the grid, 4.85 -> 4.6 clustered; FP64 at
+// offset from the particle's corner (field after field the FP32 kernel with five fields had 107 LDS reads and 126
+// integer additions, now 60 and 49; kick at 512^3: 4.65 -> 4.03 ms on the grid, 4.85 -> 4.4 - 4.8 clustered; FP64 at
 // 256^3 1.08 -> 0.98).
 template <typename T, int W> struct alignas(W * sizeof(T)) FieldVec { T f[W]; };
 
@@ -1021,7 +1021,7 @@ void launch_scan(uint32_t* cnt, uint32_t* cell_start, long ncell, uint32_t* bloc
 // scatter into the other buffer at cell_start[cell] + rank; the cell is
 // recomputed from the stored position exactly as the kick/drift computed it.
 // Bound by the scattered stores, 16 + 16 + 4 + 4 bytes apart by particles that left their neighbours
-// (512^3 FP32: 3.0 TB/s of 84 bytes each; a stream of the same bytes takes 2.6 ms of the sort's 3.9).
+// (512^3 FP32: 3.3 ms for 84 bytes each, 3.4 TB/s; a stream of the same bytes takes 2.6).
 // One particle per thread: two or four in flight gain nothing (3.92, 4.07 and 4.11 ms).
 // ---------------------------------------------------------------------------
 template <typename T>

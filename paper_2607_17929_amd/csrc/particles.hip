@@ -801,7 +801,9 @@ __global__ __launch_bounds__(KD_NT, KdShape<T>::WPE) void kick_drift_kernel(Part
     } else {
       const T chi_p = fv[1];
       const T* gchi = gf[1];
-      const T u2 = ux * ux + uy * uy + uz * uz;
+      // (the roundings of the squares are written out: which products the compiler fuses otherwise depends on how the
+      // momentum was loaded, and a hot particle's last bits with it)
+      const T u2 = fma(uz, uz, fma(uy, uy, ux * ux));
       const T ie = rsqrt_(a * a + u2);
       const T e = (a * a + u2) * ie;
       const T cphi = -(a * a + (T)2 * u2) * ie;
@@ -819,7 +821,7 @@ __global__ __launch_bounds__(KD_NT, KdShape<T>::WPE) void kick_drift_kernel(Part
       ux += dt * fx;
       uy += dt * fy;
       uz += dt * fz;
-      const T v2 = ux * ux + uy * uy + uz * uz;
+      const T v2 = fma(uz, uz, fma(ux, ux, uy * uy));
       const T eh2 = ah * ah + v2;
       const T ieh = rsqrt_(eh2);
       const T fac = ((T)1 + ((T)3 - v2 * ieh * ieh) * phi_p - chi_p) * ieh;

@@ -1,0 +1,63 @@
+"""Roundings that a run's last bits hang on, against NumPy with every rounding written out (a fused multiply-add is formed
+in FP64: the product of two FP32 values is exact there)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+F = np.float32
+
+
+def _fma(a, b, c):
+    return (np.asarray(a, np.float64) * np.asarray(b, np.float64) + np.asarray(c, np.float64)).astype(F)
+
+
+def _rsq(x):
+    """The FP32 values that an instruction accurate to one unit in the last place may give for 1 / sqrt(x)."""
+    r = (1.0 / np.sqrt(x.astype(np.float64))).astype(F)
+    return [np.nextafter(r, F(0)), r, np.nextafter(r, F(np.inf))]
+
+
+@pytest.mark.parametrize("physics", ["scalar", "full"])
+def test_kick_of_hot_particles_fp32(physics):
+    """One hot particle on every vertex of a 16^3 mesh, so that the gathered fields and gradients are the vertex's own,
+    in given phi and chi.  The squares are summed as fma(u_z, u_z, fma(u_y, u_y, u_x u_x)) before the kick and as
+    fma(u_z, u_z, fma(u_x, u_x, u_y u_y)) after it.  Momenta: equal but for two in a million (the FP64 sums in _fma are
+    rounded twice); positions: to 1e-14, where a last bit of the FP32 velocity is 1e-9."""
+    from paper_2607_17929_amd import PMContext
+    from paper_2607_17929_amd.pm import background
+    print("kick rounding", physics, flush=True)
+    n, box, tau, dtau = 16, 100.0, 12.0, 0.05
+    rng = np.random.default_rng(3)
+    ctx = PMContext(n, n ** 3, box, physics=physics, precision="fp32")
+    z, y, x = np.meshgrid(*[np.arange(n)] * 3, indexing="ij")
+    pos = np.stack([x, y, z], -1).reshape(-1, 3) / n
+    a, ah = F(background(box, tau)[0]), F(background(box, tau + 0.5 * dtau)[0])
+    u = (rng.standard_normal((n ** 3, 3)) * a).astype(F)
+    phi, chi = (0.3 * rng.standard_normal((2, n, n, n))).astype(F)
+    ctx.init_particles(pos, u, tau)
+    ctx.set_field("phi", phi)
+    ctx.set_field("chi", chi)
+    ctx.update_particles(dtau)
+    gpos, gu = ctx.get_particles()
+
+    def grad(f):
+        return [((np.roll(f, -1, ax) - np.roll(f, 1, ax)) * F(0.5 * n)).reshape(-1) for ax in (2, 1, 0)]
+
+    gp, gc, p, c = grad(phi), grad(chi), phi.reshape(-1), chi.reshape(-1)
+    ux, uy, uz = u.T
+    u2 = _fma(uz, uz, _fma(uy, uy, ux * ux))
+    e2 = a * a + u2
+    kick = drift = np.zeros(n ** 3, bool)
+    for ie in _rsq(e2):
+        cphi, e = -(a * a + F(2) * u2) * ie, e2 * ie
+        v = np.stack([_fma(F(dtau), _fma(cphi, gp[d], e * gc[d]), u[:, d]) for d in range(3)], -1)
+        kick = kick | (v == gu).all(1)
+    vx, vy, vz = gu.T
+    v2 = _fma(vz, vz, _fma(vx, vx, vy * vy))
+    for ieh in _rsq(ah * ah + v2):
+        fac = (_fma(_fma(-(v2 * ieh), ieh, 3.0), p, 1.0) - c) * ieh
+        d = gpos - (pos + dtau * (gu * fac[:, None]).astype(np.float64))
+        drift = drift | (np.abs(d - np.rint(d)).max(1) < 1e-14)
+    assert np.mean(~kick) <= 2e-6 and np.mean(~drift) <= 2e-6, (np.mean(~kick), np.mean(~drift))

@@ -85,19 +85,22 @@ void launch_ingest(const double* pos_aos, const T* u_aos, const uint32_t* ids, l
 // offsets of the staged lists are scanned in LDS, three planes in flight).
 // Only cell_start and the particle arrays are read; each vertex is written once.
 // ---------------------------------------------------------------------------
-// Workgroups of 256 threads and 32 x 8 vertex columns, on the largest meshes 128 threads and 32 x 4 (512^3 clustered
-// 4.33 ms against 4.76; at 128^3 and 256^3 they are 0.26 against 0.22 and 0.43 against 0.42 ms): one column a thread.
+// Workgroups of 256 threads and 32 x 8 vertex columns, on the largest meshes 128 threads and 32 x 4 (clustered: 512^3
+// 5.18 ms against 5.79, FP64 5.96 against 6.55, 1024^3 16.5 against 18.0; at 128^3 and 256^3 they take 0.39 against 0.37
+// and 0.45 against 0.44 ms): one column a thread.
 __host__ __device__ constexpr int dep_nt(int n) { return n >= 512 ? 128 : 256; }
 // staged particles per chunk: a plane of mean density fits one (33 x 9 or 33 x 5 cells), in FP64 with three waves a SIMD
 template <typename T, int NT> constexpr int dep_cap() { return sizeof(T) == 4 ? 2 * NT : 3 * NT / 2; }
 // Vertex planes per workgroup: 16, and fewer where that leaves fewer than DEP_WAVES waves (four rounds of 16 on
-// every CU): a 32^3 mesh in 16-plane columns is 8 workgroups that walk 17 cell planes each (78 us; 17 us with
-// single planes), a clustered 128^3 mesh 512 of them (0.38 ms; 0.25 with 8 planes, 0.22 with 4).
+// every CU): a 32^3 mesh in 16-plane columns is 8 workgroups that walk 17 cell planes each (59 us; 13 us with
+// single planes), a clustered 128^3 mesh 512 of them (0.42 ms; 0.38 with the 2 planes taken here).
 constexpr int DEP_ZB = 16, DEP_WAVES = 16384;
 // A cell of this many particles or more is summed by the whole wave on the matrix cores (crowded_cell below): in the
 // lane loop its n particles cost a lane of each of 4 vertex columns 45 n instructions while 60 others wait, here
-// n / 4 matrix products and about 100 instructions.  12 and 16 measure alike, 8 is 2 % slower (512^3 clustered,
-// cells of up to 690: deposit 5.77 -> 4.4 ms; 256^3 1.11 -> 0.80; FP64 256^3 1.47 -> 1.07 ms).
+// n / 4 matrix products and about 100 instructions (FP64, cells of up to 690: 256^3 clustered deposit 1.45 -> 1.05 ms).
+// The FP32 stress-energy stays in the lane loop: its stresses are FP32 sums that run through the particles in the
+// store's order, and in any other order or width a run's last bits change (clustered 512^3 5.18 ms, on the matrix
+// cores 4.32; 256^3 1.13 and 0.79, 128^3 0.38 and 0.22; eight lanes to a vertex, which keep the order, 5.24, 1.25, 0.45).
 constexpr uint32_t DEP_CROWD = 12;
 
 __host__ __device__ constexpr int dep_tx(int n) { return n >= 32 ? 32 : 16; }
@@ -138,7 +141,8 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
   constexpr int N4 = NC < 4 ? NC : 4, N6 = NC > 4 ? NC - 4 : 1;
   constexpr int WX = TX >= 16 ? 16 : TX, WY = 64 / WX;         // a wave's vertex columns: WX x WY
   static_assert(ROWS <= 64 && TX % WX == 0 && TY % WY == 0, "tile shape");
-  constexpr bool CROWD = NC > 1;              // (a count takes so little that the test for crowded cells costs more)
+  // (a count takes so little that the test for crowded cells costs more)
+  constexpr bool CROWD = NC == 3 || (NC > 4 && sizeof(T) == 8);
   constexpr bool VEC = NC == 3;               // sums of W v for the 3-vectors vals[id] instead of the stress-energy
   constexpr int C4 = NC > 1 ? CAP : 1, C6 = NC > 4 ? CAP : 1;
   __shared__ V4<T> sfr[CAP];                  // f_x, f_y, f_z, -
@@ -359,7 +363,8 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
       const T wx = l < (r1 ? spl[1] : spl[0]) ? fr.x : (T)1 - fr.x;
       const T wy = r1 ? (T)1 - fr.y : fr.y;
       const T wxy = wx * wy;
-      const T wh = wxy * fr.z, wl = wxy - wh;  // f_z and (1 - f_z) shares
+      // f_z and (1 - f_z) shares (the roundings of wl and of the stresses' sums are written out: runs repeat by them)
+      const T wh = wxy * fr.z, wl = fma(wx, wy, -wh);
       if constexpr (NC == 1) {
         lo4[0] += (double)(wl * a);
         hi4[0] += (double)(wh * a);
@@ -377,10 +382,10 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
         lo4[2] = fma(dl, q2, lo4[2]); lo4[3] = fma(dl, q3, lo4[3]);
         hi4[0] = fma(dh, q0, hi4[0]); hi4[1] = fma(dh, q1, hi4[1]);
         hi4[2] = fma(dh, q2, hi4[2]); hi4[3] = fma(dh, q3, hi4[3]);
-        lo6[0] += wl * t.x; lo6[1] += wl * t.y; lo6[2] += wl * t.z;
-        lo6[3] += wl * t.w; lo6[4] += wl * t4; lo6[5] += wl * t5;
-        hi6[0] += wh * t.x; hi6[1] += wh * t.y; hi6[2] += wh * t.z;
-        hi6[3] += wh * t.w; hi6[4] += wh * t4; hi6[5] += wh * t5;
+        lo6[0] = fma(wl, t.x, lo6[0]); lo6[1] = fma(wl, t.y, lo6[1]); lo6[2] = fma(wl, t.z, lo6[2]);
+        lo6[3] = fma(wl, t.w, lo6[3]); lo6[4] = fma(wl, t4, lo6[4]); lo6[5] = fma(wl, t5, lo6[5]);
+        hi6[0] = fma(wh, t.x, hi6[0]); hi6[1] = fma(wh, t.y, hi6[1]); hi6[2] = fma(wh, t.z, hi6[2]);
+        hi6[3] = fma(wh, t.w, hi6[3]); hi6[4] = fma(wh, t4, hi6[4]); hi6[5] = fma(wh, t5, hi6[5]);
       }
     }
   };

@@ -61,3 +61,42 @@ def test_kick_of_hot_particles_fp32(physics):
         d = gpos - (pos + dtau * (gu * fac[:, None]).astype(np.float64))
         drift = drift | (np.abs(d - np.rint(d)).max(1) < 1e-14)
     assert np.mean(~kick) <= 2e-6 and np.mean(~drift) <= 2e-6, (np.mean(~kick), np.mean(~drift))
+
+
+def test_deposit_fp32_stresses_are_running_sums():
+    """FP32 sums of the stresses in the order of the store: through the planes of cells, the cells in row-major order and
+    (deterministic mode) the particles of a cell by identifier, each term added with one rounding.  Cells of 60, 13, 700
+    and 5 particles next to each other; all have the same momentum, and one that sits on a vertex far off gives the
+    term itself, with weight one.  Equal but for one value in a thousand (_fma is rounded twice: 1e-9 a term)."""
+    from paper_2607_17929_amd import PMContext
+    print("deposit running sums", flush=True)
+    n = 16
+    rng = np.random.default_rng(9)
+    cells = {(4, 5, 6): 60, (5, 5, 6): 13, (4, 6, 6): 700, (5, 6, 7): 5, (5, 5, 7): 41}
+    pos = [(np.array(c) + rng.random((k, 3))) / n for c, k in cells.items()] + [np.full((1, 3), 12 / n)]
+    pos = np.concatenate(pos)
+    u = np.tile(np.array([0.11, -0.07, 0.05], F), (pos.shape[0], 1))
+    ctx = PMContext(n, pos.shape[0], 100.0, physics="scalar", precision="fp32", deterministic=True)
+    ctx.init_particles(pos, u, 12.0)
+    ctx.deposit()
+    s = pos * n
+    cell = np.floor(s).astype(int)
+    f = (s - cell).astype(F)
+    order = np.lexsort((np.arange(len(pos)), cell[:, 0], cell[:, 1], cell[:, 2]))
+    wrong = total = 0
+    for name in ("nxx", "nxy", "nxz", "nyy", "nyz", "nzz"):
+        got = ctx.get_field(name)
+        t = got[12, 12, 12]
+        want = np.zeros_like(got)
+        want[12, 12, 12] = t
+        for i in order[cell[order, 0] != 12]:
+            for dy in (0, 1):
+                for dx in (0, 1):
+                    wx, wy = f[i, 0] if dx else F(1) - f[i, 0], f[i, 1] if dy else F(1) - f[i, 1]
+                    wh = wx * wy * f[i, 2]
+                    for dz, wz in ((1, wh), (0, _fma(wx, wy, -wh))):
+                        at = (cell[i, 2] + dz, cell[i, 1] + dy, cell[i, 0] + dx)
+                        want[at] = _fma(wz, t, want[at])
+        wrong += np.sum(got != want)
+        total += np.sum(want != 0)
+    assert total > 100 and wrong <= 1e-3 * total, (wrong, total)

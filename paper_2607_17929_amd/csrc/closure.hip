@@ -101,10 +101,12 @@ __global__ __launch_bounds__(CV_NT) void conv16_kernel(const uint16_t* __restric
     v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < CV_KSTEPS; ++s) {
-      // (the 28th tap has weight zero: its lanes read the 27th's values)
+      // (the 28th tap counts as zeros, not as the 27th's values under weight zero: those may be infinite)
       const int t = 2 * s, o = ((t / 9 * CV_HY + (t / 3) % 3 + ly) * CV_HX + t % 3) * 2;
       const uint4* b = (s == CV_KSTEPS - 1) ? b0 : (t % 3 != 2 ? b1 : ((t / 3) % 3 != 2 ? b2 : b3));
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfrag[s], __builtin_bit_cast(v8bf, b[o]), acc, 0, 0, 0);
+      uint4 v = b[o];
+      if (s == CV_KSTEPS - 1 && up) v = make_uint4(0u, 0u, 0u, 0u);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfrag[s], __builtin_bit_cast(v8bf, v), acc, 0, 0, 0);
     }
     // D: lane holds output channels 4 grp + j of point col
     const long p = ((long)(z0 + lz) * n + (y0 + ly)) * n + (x0 + col);

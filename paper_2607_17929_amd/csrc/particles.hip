@@ -282,7 +282,7 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
     v4d acc = {0.0, 0.0, 0.0, 0.0};
     for (uint32_t k0 = 0; k0 < n; k0 += 4) {
       const uint32_t k = k0 + mk4;
-      const uint32_t l = b0 + min(k, n - 1);  // beyond the last particle: its values with weight zero
+      const uint32_t l = b0 + min(k, n - 1);  // (beyond the last particle: zeros, its own values may be infinite)
       const V4<T> fr = sfr[l];
       const T wx = (mcol & 1) ? fr.x : (T)1 - fr.x;
       const T wxy = wx * ((mcol & 2) ? fr.y : (T)1 - fr.y);
@@ -290,6 +290,7 @@ __global__ __launch_bounds__(DEP_NT, sizeof(T) == 4 ? 4 : 3) void deposit_kernel
       const T w8 = (k < n && mcol < 8) ? ((mcol & 4) ? wh : wxy - wh) : (T)0;
       T q = a;
       if constexpr (NC > 1) q = qbase[l * qstride];
+      if (k >= n) q = (T)0;
       acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)w8, (double)q, acc, 0, 0, 0);
     }
     // rows l / 16 (lower face) and 4 + l / 16 (upper face) of column l % 16

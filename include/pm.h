@@ -172,7 +172,8 @@ pm_status pm_deposit(pm_ctx* ctx);
 pm_status pm_solve_metric(pm_ctx* ctx, double dtau_prev);
 
 /* Stage 3: gather + kick (u to tau + dtau/2) + drift (x to tau + dtau) + re-sort;
- * tau += dtau.  Requires a preceding pm_solve_metric.  dtau > 0. */
+ * tau += dtau.  Requires a preceding pm_solve_metric and every configured species
+ * loaded (PM_ESTATE).  dtau > 0. */
 pm_status pm_update_particles(pm_ctx* ctx, double dtau);
 
 /* One whole step: deposit, solve (dtau_prev = the previous step's dtau, or a

@@ -228,6 +228,11 @@ struct pm_ctx {
     const size_t nb = (most + 4095) / 4096;
     hipLaunchKernelGGL(zero_list_kernel, dim3((unsigned)(nb < 16384 ? nb : 16384), z.count), dim3(256), 0, st, z);
   }
+  // the particle store and its cell offsets are not to be used until the next load or restore
+  void drop_particles() {
+    have_particles = have_particles2 = false;
+    deposited = solved = solved_once = cl_forwarded = false;
+  }
   // any alignment, small sizes
   void zero_bytes(unsigned char* p, size_t bytes) {
     hipLaunchKernelGGL(zero_bytes_kernel, dim3((unsigned)((bytes + 255) / 256)), dim3(256), 0, st, p, bytes);
@@ -696,6 +701,7 @@ pm_status pm_solve_metric(pm_ctx* c, double dtau_prev) {
 pm_status pm_update_particles(pm_ctx* c, double dtau) {
   if (!c) return PM_EINVAL;
   if (!c->solved) return c->fail(PM_ESTATE, "update_particles needs a preceding solve_metric");
+  if (!c->have_particles || (c->np2 > 0 && !c->have_particles2)) return c->fail(PM_ESTATE, "no particles");
   if (c->sticky) return (pm_status)c->sticky;
   if (!(dtau > 0) || !isfinite(dtau)) return c->fail(PM_EINVAL, "dtau must be positive");
   pm_status s = DISPATCH(c, do_update, c, dtau);
@@ -1197,15 +1203,13 @@ pm_status pm_set_state(pm_ctx* c, const void* blob, size_t bytes, int src_on_dev
   int flag = 0;
   if (hipMemcpyAsync(&flag, err, sizeof(int), hipMemcpyDeviceToHost, c->st) != hipSuccess ||
       hipStreamSynchronize(c->st) != hipSuccess) {
-    c->have_particles = c->have_particles2 = false;
-    c->deposited = c->solved = false;
+    c->drop_particles();
     return c->fail(PM_EHIP, "checking the restored state failed");
   }
   if (flag & 4) {
     // nothing of the blob may be used: the context has no particles until the next load or restore
     c->zero(c->L.err, 64);
-    c->have_particles = c->have_particles2 = false;
-    c->deposited = c->solved = c->solved_once = false;
+    c->drop_particles();
     return c->fail(PM_EINVAL, "state blob body inconsistent (cell offsets, positions or identifiers)");
   }
   c->cur = 0;
@@ -1309,6 +1313,7 @@ pm_status pm_closure_gather(pm_ctx* c, float* out, int dst_on_device) {
   if (s != PM_OK) return s;
   if (!out) return PM_EINVAL;
   if (!c->cl_forwarded) return c->fail(PM_ESTATE, "closure_gather needs closure_forward");
+  if (!c->have_particles) return c->fail(PM_ESTATE, "no particles");
   const Layout& L = c->L;
   const long np = c->np;
   float* dst = dst_on_device ? out : reinterpret_cast<float*>(c->ws + L.pos[1 - c->cur]);
@@ -1330,6 +1335,7 @@ pm_status pm_closure_backward(pm_ctx* c, const float* d_dpred, float* d_grad) {
   const Layout& L = c->L;
   if (!L.cl_train) return c->fail(PM_EUNSUPPORTED, "closure training needs n_mesh <= 256");
   if (!c->cl_forwarded) return c->fail(PM_ESTATE, "closure_backward needs closure_forward");
+  if (!c->have_particles) return c->fail(PM_ESTATE, "no particles");
   const int n = c->n;
   uint16_t* d3 = c->at<uint16_t>(L.cl_dact[2]);
   uint16_t* d2 = c->at<uint16_t>(L.cl_dact[1]);
@@ -1357,7 +1363,7 @@ pm_status pm_closure_loss(pm_ctx* c, const float* d_target, float* d_dpred, doub
   if (s != PM_OK) return s;
   if (!d_target || !d_dpred) return PM_EINVAL;
   if (!c->cl_forwarded) return c->fail(PM_ESTATE, "closure_loss needs closure_forward");
-  if (c->np < 1) return c->fail(PM_ESTATE, "closure_loss needs particles");
+  if (!c->have_particles) return c->fail(PM_ESTATE, "no particles");
   const Layout& L = c->L;
   double* cs = c->at<double>(L.cl_scal);
   if (c->cfg.precision == PM_FP64)

@@ -293,7 +293,7 @@ enum { PM_CLOSURE_NPARAM = 9971 };
 pm_status pm_closure_set_params(pm_ctx* ctx, const float* params, int src_on_device);
 pm_status pm_closure_enable(pm_ctx* ctx, int on);
 /* Run the network on the current deposit and phi (after pm_solve_metric); output kept in the
- * context; scaled = 1 multiplies by rms|grad phi| (force units). */
+ * context until particles are loaded or a state is restored; scaled = 1 multiplies by rms|grad phi| (force units). */
 pm_status pm_closure_forward(pm_ctx* ctx, int scaled);
 /* rms|grad phi| of the last pm_closure_forward (the output's unit); synchronises. */
 pm_status pm_closure_scale(pm_ctx* ctx, double* rms);

@@ -647,6 +647,7 @@ pm_status pm_init_particles(pm_ctx* c, const double* pos, const void* u, const u
   c->i_prev = 1;
   c->deposited = c->solved = c->solved_once = false;
   c->have_particles2 = false;  // a second species is loaded again for the new start
+  c->cl_forwarded = false;     // and the network's output was the former particles'
   pm_status s = DISPATCH(c, do_init, c, pos, u, ids, src_on_device);
   if (s != PM_OK) return s;
   c->have_particles = true;

@@ -82,3 +82,16 @@ def test_update_needs_both_species():
     ctx.init_particles_2(np.random.default_rng(3).random((77, 3)), np.zeros((77, 3), np.float32))
     ctx.set_field("phi", np.zeros((N, N, N), np.float32))
     ctx.update_particles(0.01)
+
+
+def test_forward_pass_ends_with_a_new_load():
+    """After particles are loaded anew the former set's network output and activations count no longer."""
+    print("closure calls after a reload", flush=True)
+    ctx = _ctx()
+    _load(ctx)
+    _forward(ctx)
+    assert ctx.closure_gather().shape == (NP, 3)
+    _load(ctx, 2)
+    _closure_calls_refused(ctx)
+    _forward(ctx)
+    assert ctx.closure_gather().shape == (NP, 3)

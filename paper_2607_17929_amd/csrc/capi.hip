@@ -1023,7 +1023,7 @@ struct StateHeader {
 static_assert(sizeof(StateHeader) <= kStateHeader, "state header too large");
 
 // workspace regions that make up the state: the sorted particles (as separate arrays in buffer `cur`, which is not the
-// one that holds the store), the cell offsets of the sort, phi of the latest and the previous solve and the latest
+// one that holds the store, or in a device blob itself), the cell offsets of the sort, phi of the latest and the previous solve and the latest
 // solve's increment, chi, B, the tensor and parabolic-B spectra, the FP64 scalars and, between a deposit and its
 // solve, the deposit
 int state_sections(const pm_ctx* c, int cur, int cur2, int i_phi, int i_prev, bool with_dep, size_t* ws_off,
@@ -1057,23 +1057,27 @@ int state_sections(const pm_ctx* c, int cur, int cur2, int i_phi, int i_prev, bo
   return k;
 }
 
-// the store of buffer `from` as separate arrays in buffer `to`, and back
+// the stores of buffers `buf` and `buf2` as separate arrays in the sections at sec[0 .. 2] (and sec[4 .. 6]), and back
 template <typename T>
-void state_arrays(pm_ctx* c, int from, int from2, int to, int to2, bool unpack) {
-  const Layout& L = c->L;
-  if (unpack) {
-    launch_unpack<T>(c->parts<T>(from), c->np, c->at<double>(L.pos[to]), c->at<T>(L.mom[to]),
-                     c->at<uint32_t>(L.ids[to]), (long)kSkew, c->st);
-    if (c->np2 > 0)
-      launch_unpack<T>(c->parts2<T>(from2), c->np2, c->at<double>(L.pos2[to2]), c->at<T>(L.mom2[to2]),
-                       c->at<uint32_t>(L.ids2[to2]), (long)kSkew, c->st);
-  } else {
-    launch_pack<T>(c->at<double>(L.pos[from]), c->at<T>(L.mom[from]), c->at<uint32_t>(L.ids[from]), c->np, (long)kSkew,
-                   c->parts<T>(to), c->st);
-    if (c->np2 > 0)
-      launch_pack<T>(c->at<double>(L.pos2[from2]), c->at<T>(L.mom2[from2]), c->at<uint32_t>(L.ids2[from2]), c->np2,
-                     (long)kSkew, c->parts2<T>(to2), c->st);
+void state_arrays(pm_ctx* c, int buf, int buf2, unsigned char* const* sec, bool unpack) {
+  for (int s = 0; s < (c->np2 > 0 ? 2 : 1); ++s) {
+    const Particles<T> p = s == 0 ? c->parts<T>(buf) : c->parts2<T>(buf2);
+    const long n = s == 0 ? c->np : c->np2;
+    double* pos = reinterpret_cast<double*>(sec[4 * s]);
+    T* mom = reinterpret_cast<T*>(sec[4 * s + 1]);
+    uint32_t* ids = reinterpret_cast<uint32_t*>(sec[4 * s + 2]);
+    if (unpack) launch_unpack<T>(p, n, pos, mom, ids, (long)kSkew, c->st);
+    else launch_pack<T>(pos, mom, ids, n, (long)kSkew, p, c->st);
   }
+}
+
+// A device blob's particle sections are unpacked and packed where they are, without a copy between (256^3 full FP32:
+// get 0.87 -> 0.61 ms, set 1.06 -> 0.81), if it is aligned as their values.
+bool state_in_place(const void* blob, int on_device) {
+  return on_device && reinterpret_cast<uintptr_t>(blob) % sizeof(double) == 0;
+}
+bool state_is_particles(const pm_ctx* c, int section) {
+  return section < (c->np2 > 0 ? 8 : 4) && section % 4 != 3;
 }
 
 size_t state_blob_offsets(int nsec, const size_t* bytes, uint64_t* off) {
@@ -1128,8 +1132,11 @@ pm_status pm_get_state(pm_ctx* c, void* blob, size_t* bytes, int dst_on_device) 
   for (int i = 0; i < nsec; ++i) h.bytes[i] = sb[i];
   unsigned char* dst = reinterpret_cast<unsigned char*>(blob);
   const hipMemcpyKind kind = dst_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  if (c->cfg.precision == PM_FP64) state_arrays<double>(c, c->cur, c->cur2, 1 - c->cur, 1 - c->cur2, true);
-  else state_arrays<float>(c, c->cur, c->cur2, 1 - c->cur, 1 - c->cur2, true);
+  const bool in_place = state_in_place(blob, dst_on_device);
+  unsigned char* sec[kStateMaxSec];
+  for (int i = 0; i < nsec; ++i) sec[i] = in_place ? dst + h.off[i] : c->ws + ws_off[i];
+  if (c->cfg.precision == PM_FP64) state_arrays<double>(c, c->cur, c->cur2, sec, true);
+  else state_arrays<float>(c, c->cur, c->cur2, sec, true);
   // the whole header block, zero beyond the struct
   std::vector<unsigned char> head(kStateHeader, 0);
   memcpy(head.data(), &h, sizeof(h));
@@ -1138,7 +1145,8 @@ pm_status pm_get_state(pm_ctx* c, void* blob, size_t* bytes, int dst_on_device) 
   else
     memcpy(dst, head.data(), kStateHeader);
   for (int i = 0; i < nsec; ++i) {
-    (void)hipMemcpyAsync(dst + h.off[i], c->ws + ws_off[i], sb[i], kind, c->st);
+    if (!(in_place && state_is_particles(c, i)))
+      (void)hipMemcpyAsync(dst + h.off[i], c->ws + ws_off[i], sb[i], kind, c->st);
     // zero the alignment gap after the section, so that equal states give equal blobs
     const size_t end = h.off[i] + sb[i], next = i + 1 < nsec ? h.off[i + 1] : total;
     if (next > end) {
@@ -1172,7 +1180,7 @@ pm_status pm_set_state(pm_ctx* c, const void* blob, size_t bytes, int src_on_dev
     return c->fail(PM_EINVAL, "state blob of another configuration");
   if (!(h.tau > 0) || !isfinite(h.tau) || h.steps < 0 || h.total > bytes)
     return c->fail(PM_EINVAL, "corrupt state header");
-  // restore into particle buffer 0 (by way of buffer 1) and phi slots 0 (latest), 1 (previous) and 2 (increment)
+  // restore into particle buffer 0 (by way of buffer 1, or straight from a device blob) and phi slots 0 (latest), 1 (previous) and 2 (increment)
   size_t ws_off[kStateMaxSec], sb[kStateMaxSec];
   uint64_t off[kStateMaxSec];
   const int nsec = state_sections(c, 1, 1, 0, 1, h.deposited != 0, ws_off, sb);
@@ -1182,9 +1190,15 @@ pm_status pm_set_state(pm_ctx* c, const void* blob, size_t bytes, int src_on_dev
     if (h.off[i] != off[i] || h.bytes[i] != sb[i]) return c->fail(PM_EINVAL, "corrupt state header");
   const unsigned char* src = reinterpret_cast<const unsigned char*>(blob);
   const hipMemcpyKind kind = src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-  for (int i = 0; i < nsec; ++i) (void)hipMemcpyAsync(c->ws + ws_off[i], src + off[i], sb[i], kind, c->st);
-  if (c->cfg.precision == PM_FP64) state_arrays<double>(c, 1, 1, 0, 0, false);
-  else state_arrays<float>(c, 1, 1, 0, 0, false);
+  const bool in_place = state_in_place(blob, src_on_device);
+  unsigned char* sec[kStateMaxSec];  // (only read)
+  for (int i = 0; i < nsec; ++i) {
+    const bool here = in_place && state_is_particles(c, i);
+    if (!here) (void)hipMemcpyAsync(c->ws + ws_off[i], src + off[i], sb[i], kind, c->st);
+    sec[i] = here ? const_cast<unsigned char*>(src) + off[i] : c->ws + ws_off[i];
+  }
+  if (c->cfg.precision == PM_FP64) state_arrays<double>(c, 0, 0, sec, false);
+  else state_arrays<float>(c, 0, 0, sec, false);
   // the per-cell counters are zero between sorts; the device error flag starts clear
   c->zero(c->L.cnt, c->n3 * 4);
   if (c->np2 > 0) c->zero(c->L.cnt2, c->n3 * 4);

@@ -41,19 +41,26 @@ __global__ __launch_bounds__(NT) void fft_cols_kernel(cplx<T>* data, uint32_t es
 
 // The z pass between the padded half spectrum and dense rows of n / 2 + 1 columns (the layout of a caller's spectrum):
 // the last pass of a forward transform writes them, the first of an inverse one reads them (128^3 FP32 forward and
-// back: two copies of 7 us less).  Grid: x = column tile, y = y.
+// back: two copies of 7 us less).  Dense rows start anywhere in a line, so neighbouring tiles share the lines at their
+// edges.  From 256^3 on, where a spectrum is larger than the L2s, neighbours are given to one XCD and nothing carries the
+// non-temporal hint, so that the halves of a line meet in its L2 (whole FP32 transforms, forward and back: 256^3 158 and
+// 120 -> 113 and 92 us, 512^3 1243 and 845 -> 994 and 827, 1024^3 10.5 and 7.5 -> 8.1 and 7.4 ms; with a copy between
+// padded and dense rows 138 and 122, 1097 and 1009 us, 9.4 and 8.8 ms); at 128^3 that gains nothing (22.5 and 23.3 us).
+// Grid: x = column tile, y = y.
 template <typename T, int N, int C, int NT, bool INV>
 __global__ __launch_bounds__(NT) void fft_cols_dense_kernel(const cplx<T>* in, cplx<T>* out, int nhp,
                                                             const cplx<T>* __restrict__ tw) {
   static_assert(nstages(N) >= 2, "the first stage's barrier publishes the twiddle table");
+  constexpr bool LARGE = N >= 256;
   __shared__ cplx<T> sm[N * C];
   __shared__ cplx<T> stw[N];
   for (int j = threadIdx.x; j < N; j += NT) stw[j] = tw[j];
-  constexpr int NH = N / 2 + 1;
-  const int c0 = (int)blockIdx.x * C, rin = INV ? NH : nhp, rout = INV ? nhp : NH;
-  col_stages<T, N, C, NT, 0, INV, true, true, uint32_t, false, true, true>(
-      sm, in + (long)blockIdx.y * rin + c0, (uint32_t)(N * rin), out + (long)blockIdx.y * rout + c0, (uint32_t)(N * rout),
-      stw, NH - c0);
+  constexpr int NH = N / 2 + 1, TILES = (NH + C - 1) / C;
+  const uint32_t b = blockIdx.y * TILES + blockIdx.x, l = LARGE ? xcd_remap(b, TILES * N) : b;
+  const int c0 = (int)(l % TILES) * C, rin = INV ? NH : nhp, rout = INV ? nhp : NH;
+  const long y = l / TILES;
+  col_stages<T, N, C, NT, 0, INV, true, true, uint32_t, false, !LARGE, true>(
+      sm, in + y * rin + c0, (uint32_t)(N * rin), out + y * rout + c0, (uint32_t)(N * rout), stw, NH - c0);
 }
 
 // ---------------------------------------------------------------------------

@@ -39,3 +39,19 @@ def test_power_spectrum_mode_counts(n):
         b = np.rint(np.sqrt((yz + kx * kx).astype(np.float64))).astype(np.int64)
         want += np.bincount(b, weights=w_yz * times[kx], minlength=h + 1)[:h + 1].astype(np.int64)
     assert np.array_equal(modes, want[1:])
+
+
+@pytest.mark.parametrize("precision,n", [("fp64", 256), ("fp32", 256), ("fp32", 512)])
+def test_fft_dense_rows_of_large_meshes(precision, n):
+    """Every mode and value of a transform there and back where the z pass takes its tiles in XCD order (256^3 and more,
+    the last tile one column wide), against torch's FP64 transform; bars of the small meshes' FFT test."""
+    from paper_2607_17929_amd import PMContext
+    print("fft", precision, n, flush=True)
+    ctx = PMContext(n, 8, 100.0, physics="newtonian", precision=precision)
+    f = torch.randn((n, n, n), dtype=ctx.dtype, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    fk = ctx.debug_fft(f, 1)
+    ref = torch.fft.rfftn(f.double())
+    tol = (1e-13 if precision == "fp64" else 3e-7) * np.log2(n)
+    assert float((fk.to(ref.dtype) - ref).norm() / ref.norm()) < tol
+    back = ctx.debug_fft(fk, -1)
+    assert float((back.double() - f.double()).norm() / f.double().norm()) < tol

@@ -90,6 +90,7 @@ Layout make_layout(const pm_config& c) {
   L.tw = take(n * 2 * rs);
   L.kt = take(n * rs);
   L.rowsum = take(n * n * 8);
+  static_assert(8 + MOMENTUM_SCRATCH <= 1024, "reduction scratch");
   L.scal = take(1024 * 8);  // FP64 scalars [0..8) and reduction scratch [8..1024)
   L.closure = (c.flags & PM_FLAG_CLOSURE) != 0;
   if (L.closure) {
@@ -855,17 +856,11 @@ pm_status pm_diagnostics(pm_ctx* c, double* out, int n) {
   double mom[3] = {0, 0, 0};
   for (int s = 0; s < (c->np2 > 0 ? 2 : 1); ++s) {
     const double w = s == 0 ? 1.0 : c->weight2();
-    for (int d = 0; d < 3; ++d) {
-      if (c->cfg.precision == PM_FP64) {
-        const Particles<double> p = s == 0 ? c->parts<double>(c->cur) : c->parts2<double>(c->cur2);
-        const double* u = d == 0 ? &p.b->ux : (d == 1 ? &p.c->uy : &p.c->uz);
-        launch_sum_f64(u, s == 0 ? c->np : c->np2, sc + 3 + d, c->st, 2);
-      } else {
-        const Particles<float> p = s == 0 ? c->parts<float>(c->cur) : c->parts2<float>(c->cur2);
-        const float* u = d == 0 ? &p.b->ux : (d == 1 ? &p.b->uy : &p.c->uz);
-        launch_sum_as_f64(u, s == 0 ? c->np : c->np2, sc + 3 + d, c->st, d < 2 ? 4 : 1);
-      }
-    }
+    const long n1 = s == 0 ? c->np : c->np2;
+    if (c->cfg.precision == PM_FP64)
+      launch_sum_momentum<double>(s == 0 ? c->parts<double>(c->cur) : c->parts2<double>(c->cur2), n1, sc + 3, sc + 8, c->st);
+    else
+      launch_sum_momentum<float>(s == 0 ? c->parts<float>(c->cur) : c->parts2<float>(c->cur2), n1, sc + 3, sc + 8, c->st);
     double h[6];
     if (hipMemcpyAsync(h, sc, 6 * sizeof(double), hipMemcpyDeviceToHost, c->st) != hipSuccess ||
         hipStreamSynchronize(c->st) != hipSuccess)

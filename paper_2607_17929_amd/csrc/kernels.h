@@ -99,9 +99,8 @@ template <typename T>
 void launch_tensor_components(cplx<T>* spec, long comp_stride, int n, int nhp, const T* kt, const cplx<T>* hst,
                               hipStream_t st);
 // FP64 sum of count values into out[0]; out[8 .. 8 + 512) is used as scratch
-// (values `stride` elements apart)
-void launch_sum_f64(const double* in, long count, double* out, hipStream_t st, int stride = 1);
-void launch_sum_as_f64(const float* in, long count, double* out, hipStream_t st, int stride = 1);
+void launch_sum_f64(const double* in, long count, double* out, hipStream_t st);
+void launch_sum_as_f64(const float* in, long count, double* out, hipStream_t st);
 
 // ---- pk.hip ----
 // blocks of the binning pass whose partials ((blocks + 1) rows of 3 (n/2 + 1) doubles) fit in scratch_bytes
@@ -269,6 +268,10 @@ void launch_check_store(const Particles<T>& p, long np, int nmesh, const uint32_
                         hipStream_t st);
 template <typename T>
 void launch_export(const Particles<T>& p, long np, double* pos_aos, T* u_aos, uint32_t* ids, hipStream_t st);
+// FP64 sums of the momenta's three components into out[0 .. 3), in a fixed order; scratch: MOMENTUM_SCRATCH doubles
+constexpr int MOMENTUM_SCRATCH = 3 * 320;
+template <typename T>
+void launch_sum_momentum(const Particles<T>& p, long np, double* out, double* scratch, hipStream_t st);
 
 // ---- closure.hip ----
 void closure_pack(const float* params, uint16_t* wf, uint16_t* wb, float* bias, hipStream_t st);

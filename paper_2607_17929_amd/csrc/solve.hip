@@ -386,12 +386,12 @@ void launch_tensor_components(cplx<T>* spec, long comp_stride, int n, int nhp, c
 constexpr int SUM_BLOCKS = 512;
 
 template <typename T>
-__global__ __launch_bounds__(256) void sum_partial_kernel(const T* in, long count, int stride, double* part) {
+__global__ __launch_bounds__(256) void sum_partial_kernel(const T* in, long count, double* part) {
   __shared__ double red[256];
   const long per = (count + SUM_BLOCKS - 1) / SUM_BLOCKS;
   const long b = (long)blockIdx.x * per, e = min(count, b + per);
   double acc = 0.0;
-  for (long i = b + threadIdx.x; i < e; i += 256) acc += (double)in[i * stride];
+  for (long i = b + threadIdx.x; i < e; i += 256) acc += (double)in[i];
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
@@ -417,11 +417,11 @@ __global__ __launch_bounds__(256) void sum_final_kernel(const double* part, doub
 constexpr long SUM_ONE = 16384;
 
 template <typename T>
-__global__ __launch_bounds__(1024) void sum_one_kernel(const T* in, int count, int stride, double* out) {
+__global__ __launch_bounds__(1024) void sum_one_kernel(const T* in, int count, double* out) {
   __shared__ double red[16];
   double acc = 0.0;
 #pragma unroll 4
-  for (int i = threadIdx.x; i < count; i += 1024) acc += (double)in[(long)i * stride];
+  for (int i = threadIdx.x; i < count; i += 1024) acc += (double)in[i];
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) acc += __shfl_down(acc, d);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -436,22 +436,18 @@ __global__ __launch_bounds__(1024) void sum_one_kernel(const T* in, int count, i
 
 // out[0] = sum; out[1 .. SUM_BLOCKS] is scratch for the partials
 template <typename T>
-static void sum_to_f64(const T* in, long count, double* out, hipStream_t st, int stride) {
+static void sum_to_f64(const T* in, long count, double* out, hipStream_t st) {
   if (count <= SUM_ONE) {
-    hipLaunchKernelGGL((sum_one_kernel<T>), dim3(1), dim3(1024), 0, st, in, (int)count, stride, out);
+    hipLaunchKernelGGL((sum_one_kernel<T>), dim3(1), dim3(1024), 0, st, in, (int)count, out);
     return;
   }
   static_assert(SUM_BLOCKS == 512, "final kernel adds two partials per thread");
-  hipLaunchKernelGGL((sum_partial_kernel<T>), dim3(SUM_BLOCKS), dim3(256), 0, st, in, count, stride, out + 8);
+  hipLaunchKernelGGL((sum_partial_kernel<T>), dim3(SUM_BLOCKS), dim3(256), 0, st, in, count, out + 8);
   hipLaunchKernelGGL(sum_final_kernel, dim3(1), dim3(256), 0, st, out + 8, out);
 }
 
-void launch_sum_f64(const double* in, long count, double* out, hipStream_t st, int stride) {
-  sum_to_f64<double>(in, count, out, st, stride);
-}
-void launch_sum_as_f64(const float* in, long count, double* out, hipStream_t st, int stride) {
-  sum_to_f64<float>(in, count, out, st, stride);
-}
+void launch_sum_f64(const double* in, long count, double* out, hipStream_t st) { sum_to_f64<double>(in, count, out, st); }
+void launch_sum_as_f64(const float* in, long count, double* out, hipStream_t st) { sum_to_f64<float>(in, count, out, st); }
 
 template void launch_solve<float>(const SolveArgs<float>&, hipStream_t);
 template void launch_solve<double>(const SolveArgs<double>&, hipStream_t);

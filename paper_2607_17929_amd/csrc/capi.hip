@@ -140,7 +140,7 @@ __global__ void zero_kernel(unsigned char* p, size_t bytes) {
   }
 }
 
-// Device buffers to clear in one launch (a load clears up to fourteen, a few microseconds each at any size).
+// Device buffers to clear in one launch (a load clears up to twelve, a few microseconds each at any size).
 struct ZeroList {
   static constexpr int MAX = 16;
   unsigned char* p[MAX];  // 16-byte aligned

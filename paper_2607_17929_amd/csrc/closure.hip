@@ -407,7 +407,7 @@ __global__ __launch_bounds__(256) void features_kernel(const T* __restrict__ n00
 }
 
 // ---------------------------------------------------------------------------
-// particle-side helpers: CIC gather of a 3-component FP32 SoA field and its adjoint
+// particle-side helpers: CIC gather of a 3-component FP32 SoA field
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void cic(double x, int n, int& i0, int& i1, float& w0, float& w1) {
   const double s = x * (double)n;

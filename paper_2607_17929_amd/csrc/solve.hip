@@ -280,8 +280,9 @@ __global__ __launch_bounds__(NT) void kspace_kernel(SolveArgs<T> a) {
 // 256^3 FP32 full 0.45 -> 0.33, scalar 0.217 -> 0.154 (two tiles of 4 kx: 0.166), FP64 full 0.94 -> 0.64 - 0.72.
 // FP64 with the parabolic state: 7 more values per mode are read and written, in rows of 64 and 48 bytes per kx, and
 // the whole row of 4 kx is kept where one workgroup's LDS holds it (256^3: 0.83 ms against 0.87 for tiles of 1 or 2;
-// at 512^3, where it doesn't, 6.60 - 7.32 -> 5.96 - 6.29 ms by the rule above).  FP64 full at 512^3 keeps one tile of 2 kx,
-// 5.72 - 6.05 ms from run to run: two of 1 kx take 5.50 - 5.66 in some runs and 6.51 in others.
+// at 512^3, where it doesn't, 6.60 - 7.32 -> 5.96 - 6.29 ms by the rule above).  FP64 full keeps one tile where two
+// would be had, which is at 512^3 alone: over 16 contexts its one tile of 2 kx takes 5.73 - 6.15 ms (mean 5.92), two of
+// 1 kx 5.58 - 5.79 in nine and 6.28 - 6.58 in seven (mean 6.02).
 constexpr int KS_ROW_BYTES = 256;   // contiguous bytes wanted per row of a tile
 constexpr int KS_ROW_MIN = 96;      // and not to fall below for the sake of more workgroups
 constexpr long KS_LDS[3] = {53760, 81920, 163840};  // LDS of a workgroup, three, two and one to a CU

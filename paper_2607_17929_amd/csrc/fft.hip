@@ -246,7 +246,7 @@ __global__ __launch_bounds__(NT) void fft_x_r2c_kernel(SrcArgs<T> a, cplx<T>* sp
 // LDS as [element][line] like the forward pass.
 // Bound by its bytes (512^3 FP32, 5 fields: 6.5 GB at 5.7 TB/s).  Every spectrum value is read once (the two that make
 // Z_k make Z_{M-k} too), the increment's base field is on its way before the transform, and the reals are stored in pairs:
-// 1.49 -> 1.13 ms; 256^3 0.225 -> 0.160; 1024^3 11.9 -> 9.3.
+// 1.49 -> 1.13 ms; 256^3 0.225 -> 0.160; 1024^3 12.5 -> 9.7.
 // ---------------------------------------------------------------------------
 template <typename T> struct FieldPair { T a, b; };  // (aligned as one value: a caller's array may be)
 template <typename T>

@@ -86,8 +86,8 @@ void launch_ingest(const double* pos_aos, const T* u_aos, const uint32_t* ids, l
 // Only cell_start and the particle arrays are read; each vertex is written once.
 // ---------------------------------------------------------------------------
 // Workgroups of 256 threads and 32 x 8 vertex columns, on the largest meshes 128 threads and 32 x 4 (clustered: 512^3
-// 5.18 ms against 5.79, FP64 5.96 against 6.55, 1024^3 with 512^3 particles 16.5 against 18.0; at 128^3 and 256^3 they take 0.39 against 0.37
-// and 0.45 against 0.44 ms): one column a thread.
+// 5.18 ms against 5.79, FP64 5.96 against 6.55, 1024^3 with 512^3 particles 16.5 against 18.0; at 128^3 and 256^3 they
+// take 0.39 against 0.37 and 0.45 against 0.44 ms): one column a thread.
 __host__ __device__ constexpr int dep_nt(int n) { return n >= 512 ? 128 : 256; }
 // staged particles per chunk: a plane of mean density fits one (33 x 9 or 33 x 5 cells), in FP64 with three waves a SIMD
 template <typename T, int NT> constexpr int dep_cap() { return sizeof(T) == 4 ? 2 * NT : 3 * NT / 2; }

@@ -100,3 +100,26 @@ def test_deposit_fp32_stresses_are_running_sums():
         wrong += np.sum(got != want)
         total += np.sum(want != 0)
     assert total > 100 and wrong <= 1e-3 * total, (wrong, total)
+
+
+def test_two_species_deterministic_run_repeats():
+    """Full physics, parabolic B, a hot second species, clustered cells among them: two runs of five steps, in contexts of
+    their own, are equal to the bit."""
+    from paper_2607_17929_amd import PMContext
+    print("two species, deterministic", flush=True)
+    n, n1, n2, tau = 32, 30011, 5003, 10.0
+    rng = np.random.default_rng(12)
+    pos = np.concatenate([rng.random((n1 - 4000, 3)), (0.3 + 0.02 * rng.standard_normal((4000, 3))) % 1.0])
+    u = (1e-4 * rng.standard_normal((n1, 3))).astype(F)
+    pos2, u2 = rng.random((n2, 3)), (0.2 * rng.standard_normal((n2, 3))).astype(F)
+    runs = []
+    for _ in range(2):
+        ctx = PMContext(n, n1, 128.0, physics="full", precision="fp32", b_route="parabolic", n_particles_2=n2,
+                        mass_fraction_2=0.1, deterministic=True)
+        ctx.init_particles(pos, u, tau)
+        ctx.init_particles_2(pos2, u2)
+        for _ in range(5):
+            ctx.step(0.01 * tau)
+        runs.append([*ctx.get_particles(), *ctx.get_particles_2(), *(ctx.get_field(f) for f in ("phi", "chi", "bx", "hxy"))])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
